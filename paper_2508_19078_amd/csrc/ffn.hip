@@ -11,9 +11,12 @@
 //           dw_gu   : dW_gate = dA_g^T X_s, dW_up = dA_u^T X_s  (tuning slots)
 //           dw_d    : dW_down = dO^T H                          (tuning slots)
 //
+// This file holds the large-tile bf16 and int8-weight kernels and the entry
+// points; fp32 layers and bf16 layers with few rows per slot run on the
+// small-tile kernels of ffn_tile.hip (tile_plan).
+//
 // Scheduling.  A one-block kernel turns the offsets into a schedule: prefix
-// sums of each slot's row tiles and, for the weight gradients, of each
-// tuning slot's work (its K slabs), and an order of the tuning slots by
+// sums of each slot's row tiles and an order of the tuning slots by
 // decreasing rows.  The GEMM kernels are persistent, one block per compute
 // unit.  Blocks are dispatched to the 8 XCDs round-robin, so block b runs on
 // XCD b % 8.  Row-tile products: each XCD walks its own contiguous range of the
@@ -26,39 +29,14 @@
 // draw its tiles from a counter, so that blocks that drew cheap tiles take more
 // (see DwQueue).
 #include "debug.hpp"
+#include "ffn_common.hpp"
+#include "ffn_tile.hpp"
 #include "gemm_bf16.hpp"
 
 namespace fm {
 namespace {
 
-constexpr int N_XCD = 8;
-
-struct SlotRows {
-  int nrows;    // rows of the slot
-  long orow0;   // first row of the slot in the per-row buffers
-  long xrow0;   // first row of the slot's input in X_perm (routed) or X (shared)
-  bool shared;
-};
-
-__device__ __forceinline__ SlotRows slot_rows(int s, const int32_t* offsets, int S_r, int Tn, int k) {
-  SlotRows r;
-  if (s < S_r) {
-    const int b = ld_scalar(offsets + s);
-    r.nrows = ld_scalar(offsets + s + 1) - b;
-    r.orow0 = b;
-    r.xrow0 = b;
-    r.shared = false;
-  } else {
-    r.nrows = Tn;
-    r.orow0 = (long)Tn * k + (long)(s - S_r) * Tn;
-    r.xrow0 = 0;
-    r.shared = true;
-  }
-  return r;
-}
-
-// Schedule in the workspace: mbase[0..S] (prefix of row tiles per slot),
-// wbase[0..S] (prefix of weight-gradient work per slot, 64-bit), dorder[0..S]
+// Schedule in the workspace: mbase[0..S] (prefix of row tiles per slot), dorder[0..S]
 // (the tuning slots by decreasing rows, ties by index; dorder[S] = their
 // number), the tile counters of the weight-gradient kernels (DW_QUEUES
 // queues of N_XCD counters, 128 bytes apart), zeroed by k_build_sched, and a
@@ -70,23 +48,19 @@ constexpr int DW_QINTS = DW_QUEUES * N_XCD * DW_QSTRIDE;
 constexpr int DW_SINK = 4096;      // 16-byte slots of the store sink
 struct Sched {
   int32_t* mbase;
-  long long* wbase;
   int32_t* dorder;
   int32_t* queues;
   float* sink;
 };
 inline size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 inline size_t sched_bytes(int S) {
-  return 2 * round256(sizeof(int32_t) * (S + 1)) + round256(sizeof(long long) * (S + 1)) +
-         round256(sizeof(int32_t) * DW_QINTS) + 16 * DW_SINK;
+  return 2 * round256(sizeof(int32_t) * (S + 1)) + round256(sizeof(int32_t) * DW_QINTS) + 16 * DW_SINK;
 }
 inline Sched sched_at(void* ws, int S) {
   Sched s;
   char* p = (char*)ws;
   s.mbase = (int32_t*)p;
   p += round256(sizeof(int32_t) * (S + 1));
-  s.wbase = (long long*)p;
-  p += round256(sizeof(long long) * (S + 1));
   s.dorder = (int32_t*)p;
   p += round256(sizeof(int32_t) * (S + 1));
   s.queues = (int32_t*)p;
@@ -95,48 +69,39 @@ inline Sched sched_at(void* ws, int S) {
   return s;
 }
 
-// One block of 1024 threads (S <= 1024).  The weight-gradient work of a tile
-// of a tuning slot is its number of 64-row K slabs + 1 (so an empty tuning slot
-// still gets its zeros written); frozen slots have none.
-constexpr int DW_SLAB = 64;
+// One block of 1024 threads (S <= 1023): a shuffle scan per wave, then the
+// waves' totals.  (A 1024-wide scan in LDS, two barriers for each of its ten
+// steps, made this launch 4.5-7 us.)
 __global__ __launch_bounds__(1024) void k_build_sched(const int32_t* __restrict__ offsets, int S_r, int S_sh,
                                                       int Tn, int tile_rows, float* const* __restrict__ dw_tab,
-                                                      int32_t* __restrict__ mbase, long long* __restrict__ wbase,
-                                                      int32_t* __restrict__ dorder, int32_t* __restrict__ queues) {
-  __shared__ int sm[1024];
-  __shared__ long long sw[1024];
+                                                      int32_t* __restrict__ mbase, int32_t* __restrict__ dorder,
+                                                      int32_t* __restrict__ queues) {
+  __shared__ int wsum[16];
   __shared__ int skey[1024];
-  const int S = S_r + S_sh, s = threadIdx.x;
+  const int S = S_r + S_sh, s = threadIdx.x, lane = lane_id();
   for (int i = s; i < DW_QINTS; i += 1024) queues[i] = 0;
   int n = 0;
   if (s < S) n = s < S_r ? offsets[s + 1] - offsets[s] : Tn;
   const bool tune = s < S && dw_tab && dw_tab[s];
-  long long w = 0;
-  if (tune) w = (n + DW_SLAB - 1) / DW_SLAB + 1;
-  sm[s] = (n + tile_rows - 1) / tile_rows;
-  sw[s] = w;
   skey[s] = tune ? n : -1;
-  // tuning slots by decreasing rows (ties: lower index first)
+  const int own = (n + tile_rows - 1) / tile_rows;
+  int sum = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(sum, o);
+    if (lane >= o) sum += v;
+  }
+  if (lane == 63) wsum[s >> 6] = sum;
   const int ntune = __syncthreads_count(tune);
+  for (int w = 0; w < (s >> 6); ++w) sum += wsum[w];
+  if (s <= S) mbase[s] = sum - own;
+  // tuning slots by decreasing rows (ties: lower index first)
   if (tune) {
     int rank = 0;
     for (int u = 0; u < S; ++u) rank += (skey[u] > n) || (skey[u] == n && u < s);
     dorder[rank] = s;
   }
   if (s == 0) dorder[S] = ntune;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {   // inclusive Hillis-Steele scans
-    const int a = s >= off ? sm[s - off] : 0;
-    const long long b = s >= off ? sw[s - off] : 0;
-    __syncthreads();
-    sm[s] += a;
-    sw[s] += b;
-    __syncthreads();
-  }
-  if (s <= S) {
-    mbase[s] = s == 0 ? 0 : sm[s - 1];
-    wbase[s] = s == 0 ? 0 : sw[s - 1];
-  }
 }
 
 // Largest s in [0, S) with base[s] <= v (base nondecreasing, base[0] = 0).
@@ -154,18 +119,6 @@ __device__ __forceinline__ int find_slot(const B* base, int S, long long v) {
 struct Tile {
   int s, n, m;   // slot, output column tile, output row tile
 };
-
-// Order of the (row tile, column tile) pairs of one slot: bands of GM row
-// tiles; inside a band column tiles advance slowest and row tiles fastest.  The
-// blocks of an XCD working on one band share its GM activation tiles and a few
-// weight tiles, a working set that fits the XCD's L2.
-__device__ __forceinline__ void band_order(int loc, int mt, int NT, int GM, int& m, int& n) {
-  const int band = loc / (GM * NT);
-  const int h = min(GM, mt - band * GM);
-  const int rem = loc - band * GM * NT;
-  n = rem / h;
-  m = band * GM + rem % h;
-}
 
 constexpr int GM_ROWS = 8;   // band height of the row-tile GEMMs
 constexpr int GM_DW = 4;     // band height of the weight-gradient GEMMs
@@ -188,49 +141,8 @@ __device__ __forceinline__ Tile dw_tile(long long t, int tps, int MT, int gm = G
   return r;
 }
 
-// First weight-gradient tile whose cumulative work reaches `target`; wbase
-// holds the per-tile work prefix over slots, tps tiles per slot.
-__device__ __forceinline__ long long tile_at_work(const long long* wbase, int S, int tps, long long target) {
-  if (target >= wbase[S] * tps) return (long long)S * tps;
-  const int s = find_slot(wbase, S, target / tps);
-  const long long per = wbase[s + 1] - wbase[s];
-  if (per == 0) return (long long)(s + 1) * tps;
-  long long i = (target - wbase[s] * tps + per - 1) / per;
-  if (i > tps) i = tps;
-  return (long long)s * tps + i;
-}
-
-template <typename T> struct LayerPtrs {
-  const T* const* wg;
-  const T* const* wu;
-  const T* const* wd;
-  float* const* dwg;
-  float* const* dwu;
-  float* const* dwd;
-};
-
-template <typename T> LayerPtrs<T> layer_ptrs(const moe_layer* L) {
-  return LayerPtrs<T>{(const T* const*)L->w_gate, (const T* const*)L->w_up, (const T* const*)L->w_down,
-                      L->dw_gate, L->dw_up, L->dw_down};
-}
-
-__device__ __forceinline__ float sigm(float z) { return 1.0f / (1.0f + expf(-z)); }
-// Logistic function with the hardware exp2 and reciprocal (about 1 ulp each),
-// for epilogues whose results are rounded to bf16.
-__device__ __forceinline__ float sigm_fast(float z) {
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
-}
-
-struct RowArgs {
-  const int32_t* offsets;
-  const int32_t* mbase;
-  int S_r, S, Tn, k, d, I;
-  int ldA;   // row stride (elements) of the backward's dA_g, dA_u in the workspace
-};
-
 struct DwArgs {
   const int32_t* offsets;
-  const long long* wbase;
   const int32_t* dorder;
   int32_t* queue;   // this kernel's N_XCD counters
   float* sink;      // DW_SINK 16-byte slots
@@ -256,14 +168,6 @@ __device__ __forceinline__ TileRange row_range(const RowArgs& ra, int NT) {
   return TileRange{total * x / N_XCD, total * (x + 1) / N_XCD, (int)(blockIdx.x / N_XCD),
                    (int)(gridDim.x / N_XCD)};
 }
-__device__ __forceinline__ TileRange dw_range(const DwArgs& da, int tps) {
-  const long long w = da.wbase[da.S] * tps;
-  const int x = blockIdx.x % N_XCD;
-  return TileRange{tile_at_work(da.wbase, da.S, tps, w * x / N_XCD),
-                   tile_at_work(da.wbase, da.S, tps, w * (x + 1) / N_XCD), (int)(blockIdx.x / N_XCD),
-                   (int)(gridDim.x / N_XCD)};
-}
-
 // Dynamic tile queue of the weight-gradient kernels.  XCD x owns tiles x,
 // x + 8, x + 16, ... of the tuning slots' tile space (slots in dorder, largest
 // first; tps tiles per slot), i.e. an eighth of every slot, so that the XCDs
@@ -302,235 +206,9 @@ struct DwQueue {
   }
 };
 
-// ------------------------------------------- fp32 kernels (16x16 core) ----
-
-template <typename T>
-__global__ __launch_bounds__(G_THREADS) void kf_gate_up(LayerPtrs<T> W, const T* __restrict__ X,
-                                                       const T* __restrict__ Xp, RowArgs ra,
-                                                       T* __restrict__ Ag, T* __restrict__ Au,
-                                                       T* __restrict__ H) {
-  __shared__ __align__(16) char lds[2 * (1 + 2) * GemmCfg<T>::TILE * (int)sizeof(T)];
-  const int d = ra.d, I = ra.I, NT = (I + G_BN - 1) / G_BN;
-  const TileRange tr = row_range(ra, NT);
-  for (long long t = tr.lo + tr.first; t < tr.hi; t += tr.step) {
-    const Tile rt = row_tile(ra.mbase, ra.S, NT, t);
-    const SlotRows sr = slot_rows(rt.s, ra.offsets, ra.S_r, ra.Tn, ra.k);
-    const int m0 = rt.m * G_BM, n0 = rt.n * G_BN;
-    const T* xs = (sr.shared ? X : Xp) + (size_t)(sr.xrow0 + m0) * d;
-    Opnd<T> A[1] = {{xs, d, sr.nrows - m0, d}};
-    Opnd<T> B[2] = {{ld_scalar(W.wg + rt.s) + (size_t)n0 * d, d, I - n0, d}, {ld_scalar(W.wu + rt.s) + (size_t)n0 * d, d, I - n0, d}};
-    Acc<T, 1, 2> acc;
-    acc.zero();
-    gemm_mainloop<T, true, true, 1, 2>(A, B, d, (T*)lds, acc);
-    const size_t ob = (size_t)(sr.orow0 + m0);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const AccCoord c = quad_coord<T>(q);
-      const int n = n0 + c.col4;
-      if (c.row >= sr.nrows - m0 || n >= I) continue;
-      const f32x4_t ag = acc.quad(0, q), u = acc.quad(1, q);
-      f32x4_t h;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h[r] = ag[r] * sigm(ag[r]) * u[r];
-      const size_t o = (ob + c.row) * I + n;
-      store4(Ag + o, ag);
-      store4(Au + o, u);
-      store4(H + o, h);
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(G_THREADS) void kf_down(LayerPtrs<T> W, const T* __restrict__ H, RowArgs ra,
-                                                    T* __restrict__ O) {
-  __shared__ __align__(16) char lds[2 * (1 + 1) * GemmCfg<T>::TILE * (int)sizeof(T)];
-  const int d = ra.d, I = ra.I, NT = (d + G_BN - 1) / G_BN;
-  const TileRange tr = row_range(ra, NT);
-  for (long long t = tr.lo + tr.first; t < tr.hi; t += tr.step) {
-    const Tile rt = row_tile(ra.mbase, ra.S, NT, t);
-    const SlotRows sr = slot_rows(rt.s, ra.offsets, ra.S_r, ra.Tn, ra.k);
-    const int m0 = rt.m * G_BM, n0 = rt.n * G_BN;
-    const size_t ob = (size_t)(sr.orow0 + m0);
-    Opnd<T> A[1] = {{H + ob * I, I, sr.nrows - m0, I}};
-    Opnd<T> B[1] = {{ld_scalar(W.wd + rt.s) + (size_t)n0 * I, I, d - n0, I}};
-    Acc<T, 1, 1> acc;
-    acc.zero();
-    gemm_mainloop<T, true, true, 1, 1>(A, B, I, (T*)lds, acc);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const AccCoord c = quad_coord<T>(q);
-      const int n = n0 + c.col4;
-      if (c.row >= sr.nrows - m0 || n >= d) continue;
-      store4(O + (ob + c.row) * d + n, acc.quad(0, q));
-    }
-  }
-}
-
-// ------------------------------------------------------------ backward ----
-
-// Also leaves per-row partial sums of dA_g^2 + dA_u^2 and h^2 (h = silu(a_g) a_u)
-// for the expert utility: per column tile, one pair per wave column (two),
-// at norms[row * 2 NT + 2 tile + wave column].
-template <typename T>
-__global__ __launch_bounds__(G_THREADS) void kf_dh(LayerPtrs<T> W, const T* __restrict__ dO,
-                                                  const T* __restrict__ Ag, const T* __restrict__ Au,
-                                                  RowArgs ra, T* __restrict__ dAg, T* __restrict__ dAu,
-                                                  float2* __restrict__ norms) {
-  __shared__ __align__(16) char lds[2 * (1 + 1) * GemmCfg<T>::TILE * (int)sizeof(T)];
-  const int d = ra.d, I = ra.I, NT = (I + G_BN - 1) / G_BN;
-  const TileRange tr = row_range(ra, NT);
-  for (long long t = tr.lo + tr.first; t < tr.hi; t += tr.step) {
-    const Tile rt = row_tile(ra.mbase, ra.S, NT, t);
-    const SlotRows sr = slot_rows(rt.s, ra.offsets, ra.S_r, ra.Tn, ra.k);
-    const int m0 = rt.m * G_BM, n0 = rt.n * G_BN;
-    const size_t ob = (size_t)(sr.orow0 + m0);
-    // B(n = intermediate index, k = hidden index) = W_down[k][n]: MN-contiguous
-    Opnd<T> A[1] = {{dO + ob * d, d, sr.nrows - m0, d}};
-    Opnd<T> B[1] = {{ld_scalar(W.wd + rt.s) + n0, I, I - n0, d}};
-    Acc<T, 1, 1> acc;
-    acc.zero();
-    gemm_mainloop<T, true, false, 1, 1>(A, B, d, (T*)lds, acc);
-    float sa[4] = {0.f, 0.f, 0.f, 0.f}, sh[4] = {0.f, 0.f, 0.f, 0.f};   // per row block i of the wave
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const AccCoord c = quad_coord<T>(q);
-      const int n = n0 + c.col4;
-      if (c.row >= sr.nrows - m0 || n >= I) continue;
-      const size_t o = (ob + c.row) * I + n;
-      const f32x4_t dh = acc.quad(0, q), ag = load4(Ag + o), u = load4(Au + o);
-      f32x4_t dg, du;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float s = sigm(ag[r]);
-        du[r] = dh[r] * ag[r] * s;
-        dg[r] = dh[r] * u[r] * s * (1.0f + ag[r] * (1.0f - s));
-        const float h = ag[r] * s * u[r];
-        sa[q >> 2] = fmaf(dg[r], dg[r], fmaf(du[r], du[r], sa[q >> 2]));
-        sh[q >> 2] = fmaf(h, h, sh[q >> 2]);
-      }
-      store4(dAg + o, dg);
-      store4(dAu + o, du);
-    }
-    // quad (i, j) of lane L covers row 64 wm + 16 i + L % 16: add over the
-    // four lanes L / 16 of that row, then one pair per row and wave column
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float a = sa[i], h = sh[i];
-      a += __shfl_xor(a, 16);
-      h += __shfl_xor(h, 16);
-      a += __shfl_xor(a, 32);
-      h += __shfl_xor(h, 32);
-      const int row = (wave & 1) * 64 + i * 16 + (lane & 15);
-      if (lane < 16 && row < sr.nrows - m0)
-        norms[(ob + row) * (2 * NT) + 2 * rt.n + (wave >> 1)] = make_float2(a, h);
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(G_THREADS) void kf_dx(LayerPtrs<T> W, const T* __restrict__ dAg,
-                                                  const T* __restrict__ dAu, RowArgs ra,
-                                                  T* __restrict__ dXp) {
-  __shared__ __align__(16) char lds[2 * (1 + 1) * GemmCfg<T>::TILE * (int)sizeof(T)];
-  const int d = ra.d, I = ra.I, NT = (d + G_BN - 1) / G_BN;
-  const TileRange tr = row_range(ra, NT);
-  for (long long t = tr.lo + tr.first; t < tr.hi; t += tr.step) {
-    const Tile rt = row_tile(ra.mbase, ra.S, NT, t);
-    const SlotRows sr = slot_rows(rt.s, ra.offsets, ra.S_r, ra.Tn, ra.k);
-    const int m0 = rt.m * G_BM, n0 = rt.n * G_BN;
-    const size_t ob = (size_t)(sr.orow0 + m0);
-    Acc<T, 1, 1> acc;
-    acc.zero();
-    {  // B(n = hidden index, k = intermediate index) = W_gate[k][n]
-      Opnd<T> A[1] = {{dAg + ob * I, I, sr.nrows - m0, I}};
-      Opnd<T> B[1] = {{ld_scalar(W.wg + rt.s) + n0, d, d - n0, I}};
-      gemm_mainloop<T, true, false, 1, 1>(A, B, I, (T*)lds, acc);
-    }
-    {
-      Opnd<T> A[1] = {{dAu + ob * I, I, sr.nrows - m0, I}};
-      Opnd<T> B[1] = {{ld_scalar(W.wu + rt.s) + n0, d, d - n0, I}};
-      gemm_mainloop<T, true, false, 1, 1>(A, B, I, (T*)lds, acc);
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const AccCoord c = quad_coord<T>(q);
-      const int n = n0 + c.col4;
-      if (c.row >= sr.nrows - m0 || n >= d) continue;
-      store4(dXp + (ob + c.row) * d + n, acc.quad(0, q));
-    }
-  }
-}
-
 __device__ __forceinline__ void store_dw(float* p, f32x4_t v, bool accumulate) {
   if (accumulate) v = v + load4(p);
   store4(p, v);
-}
-
-// dW_gate = dA_g^T X_s, dW_up = dA_u^T X_s: rows over I, columns over d.
-template <typename T>
-__global__ __launch_bounds__(G_THREADS) void kf_dw_gu(LayerPtrs<T> W, const T* __restrict__ X,
-                                                     const T* __restrict__ Xp, const T* __restrict__ dAg,
-                                                     const T* __restrict__ dAu, DwArgs da) {
-  __shared__ __align__(16) char lds[2 * (2 + 1) * GemmCfg<T>::TILE * (int)sizeof(T)];
-  const int d = da.d, I = da.I;
-  const int MT = (I + G_BM - 1) / G_BM, NT = (d + G_BN - 1) / G_BN;
-  const TileRange tr = dw_range(da, MT * NT);
-  for (long long t = tr.lo + tr.first; t < tr.hi; t += tr.step) {
-    const Tile rt = dw_tile(t, MT * NT, MT);
-    float* dwg = ld_scalar(W.dwg + rt.s);
-    float* dwu = ld_scalar(W.dwu + rt.s);
-    if (dwg && dwu) {
-      const SlotRows sr = slot_rows(rt.s, da.offsets, da.S_r, da.Tn, da.k);
-      const int m0 = rt.m * G_BM, n0 = rt.n * G_BN;
-      // A(m = intermediate index, k = row) = dA[row][m];  B(n = hidden index, k = row) = X_s[row][n]
-      Opnd<T> A[2] = {{dAg + (size_t)sr.orow0 * I + m0, I, I - m0, sr.nrows},
-                      {dAu + (size_t)sr.orow0 * I + m0, I, I - m0, sr.nrows}};
-      Opnd<T> B[1] = {{(sr.shared ? X : Xp) + (size_t)sr.xrow0 * d + n0, d, d - n0, sr.nrows}};
-      Acc<T, 2, 1> acc;
-      acc.zero();
-      gemm_mainloop<T, false, false, 2, 1>(A, B, sr.nrows, (T*)lds, acc);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const AccCoord c = quad_coord<T>(q);
-        const int m = m0 + c.row, n = n0 + c.col4;
-        if (m >= I || n >= d) continue;
-        store_dw(dwg + (size_t)m * d + n, acc.quad(0, q), da.accumulate);
-        store_dw(dwu + (size_t)m * d + n, acc.quad(1, q), da.accumulate);
-      }
-    }
-  }
-}
-
-// dW_down = dO^T H: rows over d, columns over I.
-template <typename T>
-__global__ __launch_bounds__(G_THREADS) void kf_dw_d(LayerPtrs<T> W, const T* __restrict__ dO,
-                                                    const T* __restrict__ H, DwArgs da) {
-  __shared__ __align__(16) char lds[2 * (1 + 1) * GemmCfg<T>::TILE * (int)sizeof(T)];
-  const int d = da.d, I = da.I;
-  const int MT = (d + G_BM - 1) / G_BM, NT = (I + G_BN - 1) / G_BN;
-  const TileRange tr = dw_range(da, MT * NT);
-  for (long long t = tr.lo + tr.first; t < tr.hi; t += tr.step) {
-    const Tile rt = dw_tile(t, MT * NT, MT);
-    float* dwd = ld_scalar(W.dwd + rt.s);
-    if (dwd) {
-      const SlotRows sr = slot_rows(rt.s, da.offsets, da.S_r, da.Tn, da.k);
-      const int m0 = rt.m * G_BM, n0 = rt.n * G_BN;
-      // A(m = hidden index, k = row) = dO[row][m];  B(n = intermediate index, k = row) = H[row][n]
-      Opnd<T> A[1] = {{dO + (size_t)sr.orow0 * d + m0, d, d - m0, sr.nrows}};
-      Opnd<T> B[1] = {{H + (size_t)sr.orow0 * I + n0, I, I - n0, sr.nrows}};
-      Acc<T, 1, 1> acc;
-      acc.zero();
-      gemm_mainloop<T, false, false, 1, 1>(A, B, sr.nrows, (T*)lds, acc);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const AccCoord c = quad_coord<T>(q);
-        const int m = m0 + c.row, n = n0 + c.col4;
-        if (m >= d || n >= I) continue;
-        store_dw(dwd + (size_t)m * I + n, acc.quad(0, q), da.accumulate);
-      }
-    }
-  }
 }
 
 // ------------------------------------------ bf16 kernels (8-wave core) ----
@@ -595,27 +273,6 @@ __device__ __forceinline__ void b16_store_staged(const B16Acc<C::MI, C::NJ>& acc
   barrier_lds_writes();
   S::template copy_out<C::RA, C::THREADS>(lds, out, ld, rows, cols);
   barrier_lds();
-}
-
-// x moved between lanes by a DPP control within each 16-lane row.
-template <int CTRL> __device__ __forceinline__ float dpp_f(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
-}
-
-// Sum of x over aligned groups of N = 16 or 32 lanes, in every lane of the
-// group: quad permutes (lane ^ 1, lane ^ 2), the half-row mirror (quad pairs)
-// and the row mirror (half-row pairs) inside each row of 16, then one exchange
-// across the two rows for N = 32.  Each step adds a lane's value to a partner
-// holding a sum over the other, equally sized part, so every lane of the group
-// ends with the same bits.
-template <int N> __device__ __forceinline__ float row_lanes_sum(float x) {
-  static_assert(N == 16 || N == 32, "one or two DPP rows");
-  x += dpp_f<0xB1>(x);    // quad_perm [1, 0, 3, 2]
-  x += dpp_f<0x4E>(x);    // quad_perm [2, 3, 0, 1]
-  x += dpp_f<0x141>(x);   // row_half_mirror
-  x += dpp_f<0x140>(x);   // row_mirror
-  if (N == 32) x += __shfl_xor(x, 16);
-  return x;
 }
 
 // SwiGLU backward of a dH tile with s = logistic(a_g): dA_u = dH a_g s,
@@ -1395,16 +1052,6 @@ int check_layer_ffn(const moe_layer* L) {
 size_t rows_total(const moe_layer* L, int T, int k) { return (size_t)T * (k + L->S_shared); }
 int n_slots(const moe_layer* L) { return L->S_routed + L->S_shared; }
 
-// Persistent grid: one block per compute unit, a multiple of the XCD count.
-int persistent_blocks() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    n = 256;
-  n = (n / N_XCD) * N_XCD;
-  return n < N_XCD ? N_XCD : n;
-}
-
 }  // namespace
 }  // namespace fm
 
@@ -1415,12 +1062,10 @@ extern "C" size_t moe_grouped_swiglu_fwd_workspace_size(const moe_layer* L, int 
   return sched_bytes(n_slots(L));
 }
 
-// Rows per row tile of the backward (bf16 or fp32 core).
-static int bwd_tile_rows(const moe_layer* L) { return L->dtype == MOE_BF16 ? B16_ROWS : G_BM; }
-// Partials of the utility's row norms per row: one per dH column tile (bf16),
-// two per column tile (fp32, one per wave column).
-static int norm_parts(const moe_layer* L) {
-  return L->dtype == MOE_BF16 ? (L->I + CB::RB - 1) / CB::RB : 2 * ((L->I + G_BN - 1) / G_BN);
+// Partials of the utility's row norms per row: one per dH column tile.
+static int norm_parts(const moe_layer* L, int T, int k) {
+  const TilePlan p = tile_plan(L, T, k);
+  return cdiv(L->I, p.rows == TilePlan::LARGE_ROWS ? CB::RB : tile_norm_cols(L, p));
 }
 
 // Backward workspace: schedule | dA_g | dA_u | per-row norm partials (float2) |
@@ -1447,7 +1092,7 @@ static BwdWs bwd_ws_at(void* ws, const moe_layer* L, int T, int k) {
   w.dAu = p + act;
   p += 2 * act;
   w.norms = (float2*)p;
-  p += round256(sizeof(float2) * rows_total(L, T, k) * norm_parts(L));
+  p += round256(sizeof(float2) * rows_total(L, T, k) * norm_parts(L, T, k));
   w.vrow = (double*)p;
   return w;
 }
@@ -1455,7 +1100,7 @@ static BwdWs bwd_ws_at(void* ws, const moe_layer* L, int T, int k) {
 extern "C" size_t moe_grouped_swiglu_bwd_workspace_size(const moe_layer* L, int T, int k) {
   if (!L || T < 0 || k <= 0) return 0;
   return sched_bytes(n_slots(L)) + 2 * bwd_act_bytes(L, T, k) +
-         round256(sizeof(float2) * rows_total(L, T, k) * norm_parts(L)) +
+         round256(sizeof(float2) * rows_total(L, T, k) * norm_parts(L, T, k)) +
          round256(sizeof(double) * rows_total(L, T, k));
 }
 
@@ -1477,26 +1122,20 @@ extern "C" int moe_grouped_swiglu_fwd(const moe_layer* L, const void* X, const v
                 moe_grouped_swiglu_fwd_workspace_size(L, T, k));
   hipStream_t st = as_stream(stream);
   if (debug_checks() && L->S_routed > 0) FM_TRY(debug_check_offsets(offsets, L->S_routed, T, k, st));
+  const TilePlan plan = tile_plan(L, T, k);
+  if (plan.rows != TilePlan::LARGE_ROWS) {
+    tile_fwd(plan, L, X, X_perm, offsets, T, k, A_g, A_u, H, O, st);
+    return check_launch("moe_grouped_swiglu_fwd");
+  }
   const int S = n_slots(L);
   const Sched sc = sched_at(ws, S);
-  const int tile_rows = bwd_tile_rows(L);
-  hipLaunchKernelGGL(k_build_sched, dim3(1), dim3(1024), 0, st, offsets, L->S_routed, L->S_shared, T, tile_rows,
-                     (float* const*)nullptr, sc.mbase, sc.wbase, sc.dorder, sc.queues);
+  hipLaunchKernelGGL(k_build_sched, dim3(1), dim3(1024), 0, st, offsets, L->S_routed, L->S_shared, T, B16_ROWS,
+                     (float* const*)nullptr, sc.mbase, sc.dorder, sc.queues);
   const RowArgs ra{offsets, sc.mbase, L->S_routed, S, T, k, L->d, L->I, L->I};
-  const dim3 grid(persistent_blocks()), block(G_THREADS);
-#define FM_FWD(TT)                                                                                      \
-  hipLaunchKernelGGL(kf_gate_up<TT>, grid, block, 0, st, layer_ptrs<TT>(L), (const TT*)X, (const TT*)X_perm, \
-                     ra, (TT*)A_g, (TT*)A_u, (TT*)H);                                                   \
-  hipLaunchKernelGGL(kf_down<TT>, grid, block, 0, st, layer_ptrs<TT>(L), (const TT*)H, ra, (TT*)O);
-  if (L->dtype == MOE_BF16) {
-    const dim3 b8(CB::THREADS);
-    hipLaunchKernelGGL(kb_gate_up, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, ra, (bf16*)A_g,
-                       (bf16*)A_u, (bf16*)H);
-    hipLaunchKernelGGL(kb_down, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)H, ra, (bf16*)O);
-  } else {
-    FM_FWD(float)
-  }
-#undef FM_FWD
+  const dim3 grid(persistent_blocks()), block(CB::THREADS);
+  hipLaunchKernelGGL(kb_gate_up, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, ra, (bf16*)A_g,
+                     (bf16*)A_u, (bf16*)H);
+  hipLaunchKernelGGL(kb_down, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)H, ra, (bf16*)O);
   return check_launch("moe_grouped_swiglu_fwd");
 }
 
@@ -1534,7 +1173,7 @@ extern "C" int moe_grouped_swiglu_fwd_q8(const moe_layer_q8* L, const void* X, c
   const int S = L->S_routed + L->S_shared;
   const Sched sc = sched_at(ws, S);
   hipLaunchKernelGGL(k_build_sched, dim3(1), dim3(1024), 0, st, offsets, L->S_routed, L->S_shared, T, CQ::RA,
-                     (float* const*)nullptr, sc.mbase, sc.wbase, sc.dorder, sc.queues);
+                     (float* const*)nullptr, sc.mbase, sc.dorder, sc.queues);
   const RowArgs ra{offsets, sc.mbase, L->S_routed, S, T, k, L->d, L->I, L->I};
   const Q8Ptrs W{L->q_gate, L->q_up, L->q_down, L->s_gate, L->s_up, L->s_down};
   const dim3 grid(persistent_blocks()), block(CQ::THREADS);
@@ -1575,51 +1214,46 @@ extern "C" int moe_grouped_swiglu_bwd(const moe_layer* L, const void* X, const v
   char* dAg = bw.dAg;
   char* dAu = bw.dAu;
   const int d = L->d, I = L->I;
-  const int tile_rows = bwd_tile_rows(L);
-  hipLaunchKernelGGL(k_build_sched, dim3(1), dim3(1024), 0, st, offsets, L->S_routed, L->S_shared, T, tile_rows,
-                     L->dw_gate, sc.mbase, sc.wbase, sc.dorder, sc.queues);
   const int ldA = act_ld(L);
+  const TilePlan plan = tile_plan(L, T, k);
+  const bool big_rows = plan.rows == TilePlan::LARGE_ROWS, big_dw = plan.dw == TilePlan::LARGE_DW;
+  if (big_rows || big_dw)   // the small-tile kernels need no schedule
+    hipLaunchKernelGGL(k_build_sched, dim3(1), dim3(1024), 0, st, offsets, L->S_routed, L->S_shared, T, B16_ROWS,
+                       L->dw_gate, sc.mbase, sc.dorder, sc.queues);
   const RowArgs ra{offsets, sc.mbase, L->S_routed, S, T, k, d, I, ldA};
-  const DwArgs da{offsets, sc.wbase, sc.dorder, sc.queues, sc.sink, L->S_routed, S, T, k, d, I, accumulate_dw,
-                  ldA};
+  const DwArgs da{offsets, sc.dorder, sc.queues, sc.sink, L->S_routed, S, T, k, d, I, accumulate_dw, ldA};
   DwArgs da_d = da;
   da_d.queue = sc.queues + N_XCD * DW_QSTRIDE;
-  const dim3 grid(persistent_blocks()), block(G_THREADS);
-#define FM_BWD(TT)                                                                                        \
-  if (T > 0) {                                                                                            \
-    hipLaunchKernelGGL(kf_dh<TT>, grid, block, 0, st, layer_ptrs<TT>(L), (const TT*)dO, (const TT*)A_g,   \
-                       (const TT*)A_u, ra, (TT*)dAg, (TT*)dAu, bw.norms);                                \
-    hipLaunchKernelGGL(kf_dx<TT>, grid, block, 0, st, layer_ptrs<TT>(L), (const TT*)dAg, (const TT*)dAu, \
-                       ra, (TT*)dX_perm);                                                                \
-  }                                                                                                       \
-  hipLaunchKernelGGL(kf_dw_gu<TT>, grid, block, 0, st, layer_ptrs<TT>(L), (const TT*)X, (const TT*)X_perm, \
-                     (const TT*)dAg, (const TT*)dAu, da);                                                \
-  hipLaunchKernelGGL(kf_dw_d<TT>, grid, block, 0, st, layer_ptrs<TT>(L), (const TT*)dO, (const TT*)H, da);
-  if (L->dtype == MOE_BF16) {
-    // dX goes last (both weight gradients first): the permutation backward
-    // that follows reads dX_perm while it is still in the memory-side cache
-    // (measured 79 -> 62 us for it at T = 8192, d = 2048, k = 6 + 2 shared,
-    // with the 1.45 GB of fp32 weight gradients written before dX instead of
-    // between dX and that read).
-    const dim3 b8(CB::THREADS);
-    if (T > 0)
-      hipLaunchKernelGGL(kb_dh, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)A_g, (cbp)A_u, ra,
-                         (bf16*)dAg, (bf16*)dAu, bw.norms);
-    if (accumulate_dw) {
-      hipLaunchKernelGGL(kb_dw_d<true>, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)H, da_d);
-      hipLaunchKernelGGL(kb_dw_gu<true>, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, (cbp)dAg,
-                         (cbp)dAu, da);
-    } else {
-      hipLaunchKernelGGL(kb_dw_d<false>, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)H, da_d);
-      hipLaunchKernelGGL(kb_dw_gu<false>, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, (cbp)dAg,
-                         (cbp)dAu, da);
-    }
-    if (T > 0)
-      hipLaunchKernelGGL(kb_dx, grid, b8, 0, st, layer_ptrs<bf16>(L), (cbp)dAg, (cbp)dAu, ra, (bf16*)dX_perm);
-  } else {
-    FM_BWD(float)
+  const dim3 grid(persistent_blocks()), block(CB::THREADS);
+  // dX goes last (both weight gradients first): the permutation backward
+  // that follows reads dX_perm while it is still in the memory-side cache
+  // (measured 79 -> 62 us for it at T = 8192, d = 2048, k = 6 + 2 shared,
+  // with the 1.45 GB of fp32 weight gradients written before dX instead of
+  // between dX and that read).
+  if (T > 0) {
+    if (big_rows)
+      hipLaunchKernelGGL(kb_dh, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)A_g, (cbp)A_u, ra, (bf16*)dAg,
+                         (bf16*)dAu, bw.norms);
+    else
+      tile_dh(plan, L, offsets, T, k, A_g, A_u, dO, dAg, dAu, ldA, bw.norms, st);
   }
-#undef FM_BWD
+  if (!big_dw) {
+    tile_dw(plan, L, X, X_perm, offsets, T, k, H, dO, dAg, dAu, ldA, accumulate_dw, st);
+  } else if (accumulate_dw) {
+    hipLaunchKernelGGL(kb_dw_d<true>, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)H, da_d);
+    hipLaunchKernelGGL(kb_dw_gu<true>, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, (cbp)dAg,
+                       (cbp)dAu, da);
+  } else {
+    hipLaunchKernelGGL(kb_dw_d<false>, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)H, da_d);
+    hipLaunchKernelGGL(kb_dw_gu<false>, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, (cbp)dAg,
+                       (cbp)dAu, da);
+  }
+  if (T > 0) {
+    if (big_rows)
+      hipLaunchKernelGGL(kb_dx, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)dAg, (cbp)dAu, ra, (bf16*)dX_perm);
+    else
+      tile_dx(plan, L, offsets, T, k, dAg, dAu, ldA, dX_perm, st);
+  }
   return check_launch("moe_grouped_swiglu_bwd");
 }
 
@@ -1657,7 +1291,7 @@ extern "C" int moe_expert_utility(const moe_layer* L, const float* x_sq, const f
   const RowArgs ra{offsets, nullptr, L->S_routed, S, T, k, L->d, L->I, act_ld(L)};
   hipLaunchKernelGGL(k_utility_rows, dim3((unsigned)cdiv((long long)rows_total(L, T, k), UT_THREADS)),
                      dim3(UT_THREADS), 0, st, ra, perm_token, perm_gate, x_sq, dy_sq, (const float2*)bw.norms,
-                     norm_parts(L), bw.vrow);
+                     norm_parts(L, T, k), bw.vrow);
   hipLaunchKernelGGL(k_utility_slots, dim3((unsigned)S), dim3(US_THREADS), 0, st, ra, (const double*)bw.vrow,
                      utility);
   return check_launch("moe_expert_utility");

@@ -1,0 +1,601 @@
+// Grouped SwiGLU expert FFN on small tiles: fp32 layers, and bf16 layers whose
+// slots hold few rows (see tile_plan).  Same rows, outputs and rounding points
+// as the large-tile kernels of ffn.hip.
+//
+// A kernel needs no schedule from an earlier launch: every block turns the
+// offsets into its own prefix of row tiles per slot in LDS (a block scan, about
+// a microsecond, against a launch of its own for a schedule kernel) and finds a
+// tile's slot with a ballot over that prefix.  Blocks are dealt to the 8 XCDs
+// round-robin; each XCD walks its own contiguous range of a row product's
+// tiles, so that the row tiles of a slot that share a weight tile meet in one
+// L2.  Weight-gradient tiles are dealt over all blocks, the slots with most rows
+// first, since a tile's cost is its slot's rows.
+//
+// What bounds them.  fp32: the matrix pipe (157 TFLOP/s), 77 % busy at 24000
+// rows, d = 1024, I = 768 (forward + backward 2.87 ms); a step of T = 1023, d =
+// 1000, I = 616, 16 + 1 experts takes 0.68 ms (1.14 with a 128 x 128 tile per
+// compute unit, register-staged, one slab ahead), one of 256 tokens, d = 128, I =
+// 256 113 us (213).  bf16 with few rows per slot: the weights' bytes; at T = 64,
+// d = 2048, I = 1408, 64 slots gate-up streams 738 MB in 97 us (126 on 256-row
+// tiles, which leave one block per compute unit and 9 of 10 rows empty), down 50
+// (75), dH 51 (94), dX 145 (183: k-major rows 4 KB apart share L2 channels).
+#include "ffn_common.hpp"
+#include "ffn_tile.hpp"
+#include "gemm_tile.hpp"
+
+namespace fm {
+namespace {
+
+constexpr int MAX_S = 1023;   // slots of a layer (512 routed + 511 shared)
+
+// Block prefix of row tiles: pre[s] = tiles of the slots before s, s in [0, S].
+__device__ __forceinline__ void tile_sched(int* pre, int* wsum, const RowArgs& ra, int tile_rows) {
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  int carry = 0;
+  for (int b = 0; b < ra.S; b += 256) {
+    const int s = b + tid;
+    int n = 0;
+    if (s < ra.S) {
+      const int rows = s < ra.S_r ? ra.offsets[s + 1] - ra.offsets[s] : ra.Tn;
+      n = (rows + tile_rows - 1) / tile_rows;
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(n, o);
+      if (lane >= o) n += v;
+    }
+    if (lane == 63) wsum[wave] = n;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int v = wsum[w];
+      if (w < wave) n += v;
+    }
+    if (s < ra.S) pre[s + 1] = carry + n;
+    carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    __syncthreads();
+  }
+  if (tid == 0) pre[0] = 0;
+  __syncthreads();
+}
+
+// The slot of row tile m: the number of slots whose tiles all lie before it.
+__device__ __forceinline__ int tile_slot(const int* pre, int S, int m) {
+  int c = 0;
+  for (int b = 0; b < S; b += 64) {
+    const int s = b + lane_id();
+    c += __builtin_popcountll(__ballot(s < S && pre[s + 1] <= m));
+  }
+  return __builtin_amdgcn_readfirstlane(c);
+}
+
+// One row tile: its slot's rows from the tile's first on, and its column tile.
+struct RowTile {
+  SlotRows sr;
+  int s, m0, n;
+  int rows;     // rows of the slot from m0 on
+  size_t ob;    // first row in the per-row buffers
+};
+__device__ __forceinline__ RowTile row_tile_at(const int* pre, const RowArgs& ra, int t, int NT, int RA) {
+  RowTile r;
+  r.s = tile_slot(pre, ra.S, t / NT);
+  const int mb = __builtin_amdgcn_readfirstlane(pre[r.s]);
+  const int mt = __builtin_amdgcn_readfirstlane(pre[r.s + 1]) - mb;
+  int m;
+  band_order(t - mb * NT, mt, NT, 8, m, r.n);
+  r.sr = slot_rows(r.s, ra.offsets, ra.S_r, ra.Tn, ra.k);
+  r.m0 = m * RA;
+  r.rows = r.sr.nrows - r.m0;
+  r.ob = (size_t)(r.sr.orow0 + r.m0);
+  return r;
+}
+
+// This block's tiles of a row product: [lo, hi) by step, the XCD's own range.
+struct Span {
+  int lo, hi, step;
+};
+__device__ __forceinline__ Span row_span(const int* pre, const RowArgs& ra, int NT) {
+  const long long total = (long long)pre[ra.S] * NT;
+  const int x = blockIdx.x % N_XCD;
+  return Span{__builtin_amdgcn_readfirstlane((int)(total * x / N_XCD)) + (int)(blockIdx.x / N_XCD),
+              __builtin_amdgcn_readfirstlane((int)(total * (x + 1) / N_XCD)), (int)(gridDim.x / N_XCD)};
+}
+
+template <typename T> __device__ __forceinline__ float tile_sigm(float z) { return sigm(z); }
+template <> __device__ __forceinline__ float tile_sigm<bf16>(float z) { return sigm_fast(z); }
+
+template <class C> __device__ __forceinline__ AccCoord tile_coord(int i, int j, int q) {
+  const int lane = lane_id(), wave = wave_id();
+  return AccCoord{(wave % C::WM) * C::TM + i * 32 + (lane & 31),
+                  (wave / C::WM % C::WN) * C::TN + j * 32 + 8 * q + 4 * (lane >> 5)};
+}
+
+// Whether this wave holds accumulators after tile_gemm (the waves with wk = 0).
+template <class C> __device__ __forceinline__ bool tile_holds() {
+  return C::WK == 1 || wave_id() < C::WM * C::WN;
+}
+
+// Puts a block's accumulators into LDS as an RA x RB tile of TO.
+template <class C, typename TO>
+__device__ __forceinline__ void tile_stage(const B16Acc<C::MI, C::NJ>& acc, FM_LDS char* lds) {
+  static_assert(C::RA * C::RB * (int)sizeof(TO) <= C::LDS, "staged tile");
+  using S = Stage<TO, C::RB>;
+  if (tile_holds<C>()) {
+#pragma unroll
+    for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < C::NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const AccCoord c = tile_coord<C>(i, j, q);
+          S::put4(lds, c.row, c.col4, acc.quad(i, j, q));
+        }
+  }
+  barrier_lds_writes();
+}
+
+// [A_g | A_u] = X_s [W_gate | W_up]^T, H = silu(A_g) A_u from A_g, A_u as
+// stored.  The B tile interleaves 32-row blocks of W_gate and W_up: RB / 2
+// intermediate columns per tile.
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_gate_up(LayerPtrs<typename C::T> W,
+                                                          const typename C::T* __restrict__ X,
+                                                          const typename C::T* __restrict__ Xp, RowArgs ra,
+                                                          typename C::T* __restrict__ Ag,
+                                                          typename C::T* __restrict__ Au,
+                                                          typename C::T* __restrict__ H) {
+  typedef typename C::T T;
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ int pre[MAX_S + 1];
+  __shared__ int wsum[4];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  constexpr int CI = C::RB / 2;
+  using SG = Stage<T, CI>;
+  const int d = ra.d, I = ra.I, NT = (I + CI - 1) / CI;
+  tile_sched(pre, wsum, ra, C::RA);
+  const Span sp = row_span(pre, ra, NT);
+  for (int t = sp.lo; t < sp.hi; t += sp.step) {
+    const RowTile r = row_tile_at(pre, ra, t, NT, C::RA);
+    const int n0 = r.n * CI, cols = I - n0;
+    const TileSrc<T> A{(r.sr.shared ? X : Xp) + (size_t)(r.sr.xrow0 + r.m0) * d, nullptr, nullptr, d, r.rows};
+    const TileSrc<T> B{ld_scalar(W.wg + r.s) + (size_t)n0 * d, ld_scalar(W.wu + r.s) + (size_t)n0 * d, nullptr, d, cols};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, true, true, false, true>(A, B, d, lds, acc);
+    FM_LDS char* const sg = lds;
+    FM_LDS char* const su = lds + C::RA * CI * (int)sizeof(T);
+    if (tile_holds<C>()) {
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const AccCoord c = tile_coord<C>(i, j, q);
+            SG::put4((c.col4 >> 5) & 1 ? su : sg, c.row, 32 * (c.col4 >> 6) + (c.col4 & 31), acc.quad(i, j, q));
+          }
+    }
+    barrier_lds_writes();
+    const int tid = wave_id() * 64 + lane_id_here();
+#pragma unroll 2
+    for (int idx = tid; idx < C::RA * SG::CPR; idx += 256) {
+      const int row = idx / SG::CPR, c = idx % SG::CPR;
+      const uint32_t off = row * SG::ROW_BYTES + ((c ^ (row & (SG::CPR - 1))) << 4);
+      const u32x4_t g = *(const FM_LDS u32x4_t*)(sg + off);
+      const u32x4_t u = *(const FM_LDS u32x4_t*)(su + off);
+      if (row < r.rows && c * SG::EPC < cols) {
+        const size_t o = (r.ob + row) * I + n0 + c * SG::EPC;
+        float a[SG::EPC], v[SG::EPC], h[SG::EPC];
+        unpack16(g, a, (T*)nullptr);
+        unpack16(u, v, (T*)nullptr);
+#pragma unroll
+        for (int e = 0; e < SG::EPC; ++e) h[e] = a[e] * tile_sigm<T>(a[e]) * v[e];
+        st16(Ag + o, g);
+        st16(Au + o, u);
+        st16(H + o, pack16(h, (T*)nullptr));
+      }
+    }
+    barrier_lds();
+  }
+}
+
+// O = H W_down^T.
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_down(LayerPtrs<typename C::T> W,
+                                                       const typename C::T* __restrict__ H, RowArgs ra,
+                                                       typename C::T* __restrict__ O) {
+  typedef typename C::T T;
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ int pre[MAX_S + 1];
+  __shared__ int wsum[4];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  const int d = ra.d, I = ra.I, NT = (d + C::RB - 1) / C::RB;
+  tile_sched(pre, wsum, ra, C::RA);
+  const Span sp = row_span(pre, ra, NT);
+  for (int t = sp.lo; t < sp.hi; t += sp.step) {
+    const RowTile r = row_tile_at(pre, ra, t, NT, C::RA);
+    const int n0 = r.n * C::RB;
+    const TileSrc<T> A{H + r.ob * I, nullptr, nullptr, I, r.rows};
+    const TileSrc<T> B{ld_scalar(W.wd + r.s) + (size_t)n0 * I, nullptr, nullptr, I, d - n0};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, true, true>(A, B, I, lds, acc);
+    tile_stage<C, T>(acc, lds);
+    Stage<T, C::RB>::template copy_out<C::RA, 256>(lds, O + r.ob * d + n0, d, r.rows, d - n0);
+    barrier_lds();
+  }
+}
+
+// dH = dO W_down (B = W_down read k-major), rounded to T, then the SwiGLU
+// backward in 16-byte row chunks; per row and column tile the sums of
+// dA_g^2 + dA_u^2 and h^2 go to norms[row * NT + n] (the expert utility).
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_dh(LayerPtrs<typename C::T> W,
+                                                     const typename C::T* __restrict__ dO,
+                                                     const typename C::T* __restrict__ Ag,
+                                                     const typename C::T* __restrict__ Au, RowArgs ra,
+                                                     typename C::T* __restrict__ dAg,
+                                                     typename C::T* __restrict__ dAu, float2* __restrict__ norms) {
+  typedef typename C::T T;
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ int pre[MAX_S + 1];
+  __shared__ int wsum[4];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  using S = Stage<T, C::RB>;
+  constexpr int V = C::V, CH = S::CPR, PER = C::RA * CH / 256, G = PER < 4 ? PER : 4;
+  static_assert(C::RA * CH % 256 == 0 && PER % G == 0, "whole chunks per lane");
+  const int d = ra.d, I = ra.I, NT = (I + C::RB - 1) / C::RB;
+  tile_sched(pre, wsum, ra, C::RA);
+  const Span sp = row_span(pre, ra, NT);
+  for (int t = sp.lo; t < sp.hi; t += sp.step) {
+    const RowTile r = row_tile_at(pre, ra, t, NT, C::RA);
+    const int n0 = r.n * C::RB, cols = I - n0;
+    const TileSrc<T> A{dO + r.ob * d, nullptr, nullptr, d, r.rows};
+    const TileSrc<T> B{ld_scalar(W.wd + r.s) + n0, nullptr, nullptr, I, cols};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, true, false>(A, B, d, lds, acc);
+    // A_g, A_u of the first chunks are on their way while the tile is staged
+    const int tid = wave_id() * 64 + lane_id_here();
+    u32x4_t ga[G], ua[G];
+    auto load = [&](int g) {
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int idx = tid + (g * G + u) * 256, row = idx / CH, c = (idx % CH) * V;
+        if (row < r.rows && c < cols) {
+          const size_t o = (r.ob + row) * I + n0 + c;
+          ga[u] = ld16(Ag + o);
+          ua[u] = ld16(Au + o);
+        }
+      }
+    };
+    load(0);
+    tile_stage<C, T>(acc, lds);
+#pragma unroll
+    for (int g = 0; g < PER / G; ++g) {
+      if (g > 0) load(g);
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int idx = tid + (g * G + u) * 256, row = idx / CH, c = (idx % CH) * V;
+        float sa = 0.f, sh = 0.f;
+        if (row < r.rows && c < cols) {
+          const size_t oo = (r.ob + row) * ra.ldA + n0 + c;
+          float dh[V], a[V], up[V], dg[V], du[V];
+          const u32x4_t hv = *(const FM_LDS u32x4_t*)(lds + S::at(row, c));
+          unpack16(hv, dh, (T*)nullptr);
+          unpack16(ga[u], a, (T*)nullptr);
+          unpack16(ua[u], up, (T*)nullptr);
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            const float sg = tile_sigm<T>(a[e]);
+            const float silu = a[e] * sg;
+            du[e] = dh[e] * silu;
+            dg[e] = dh[e] * up[e] * sg * (1.0f + a[e] * (1.0f - sg));
+            const float h = silu * up[e];
+            sa = fmaf(dg[e], dg[e], fmaf(du[e], du[e], sa));
+            sh = fmaf(h, h, sh);
+          }
+          st16(dAg + oo, pack16(dg, (T*)nullptr));
+          st16(dAu + oo, pack16(du, (T*)nullptr));
+        }
+        sa = row_lanes_sum<CH>(sa);
+        sh = row_lanes_sum<CH>(sh);
+        if ((tid & (CH - 1)) == 0 && row < r.rows) norms[(r.ob + row) * NT + r.n] = make_float2(sa, sh);
+      }
+    }
+    barrier_lds();
+  }
+}
+
+// dX_s = dA_g W_gate + dA_u W_up (B read k-major) as one k loop.
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_dx(LayerPtrs<typename C::T> W,
+                                                     const typename C::T* __restrict__ dAg,
+                                                     const typename C::T* __restrict__ dAu, RowArgs ra,
+                                                     typename C::T* __restrict__ dXp) {
+  typedef typename C::T T;
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ int pre[MAX_S + 1];
+  __shared__ int wsum[4];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  const int d = ra.d, I = ra.I, NT = (d + C::RB - 1) / C::RB;
+  tile_sched(pre, wsum, ra, C::RA);
+  const Span sp = row_span(pre, ra, NT);
+  for (int t = sp.lo; t < sp.hi; t += sp.step) {
+    const RowTile r = row_tile_at(pre, ra, t, NT, C::RA);
+    const int n0 = r.n * C::RB;
+    const TileSrc<T> A{dAg + r.ob * ra.ldA, nullptr, dAu + r.ob * ra.ldA, ra.ldA, r.rows};
+    const TileSrc<T> B{ld_scalar(W.wg + r.s) + n0, nullptr, ld_scalar(W.wu + r.s) + n0, d, d - n0};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, true, false, false, false, true>(A, B, I, lds, acc);
+    tile_stage<C, T>(acc, lds);
+    Stage<T, C::RB>::template copy_out<C::RA, 256>(lds, dXp + r.ob * d + n0, d, r.rows, d - n0);
+    barrier_lds();
+  }
+}
+
+// The tuning slots, most rows first (ties: lower index), in order[0 .. n);
+// key: S ints of LDS, free again on return.
+__device__ __forceinline__ int tile_dw_order(FM_LDS int* key, short* order, const RowArgs& ra,
+                                             float* const* dw_tab) {
+  int n = 0;
+  for (int b = 0; b < ra.S; b += 256) {
+    const int s = b + threadIdx.x;
+    bool tune = false;
+    if (s < ra.S) {
+      tune = dw_tab[s] != nullptr;
+      key[s] = !tune ? -1 : s < ra.S_r ? ra.offsets[s + 1] - ra.offsets[s] : ra.Tn;
+    }
+    n += __syncthreads_count(tune);
+  }
+  for (int s = threadIdx.x; s < ra.S; s += 256) {
+    const int rows = key[s];
+    if (rows < 0) continue;
+    int rank = 0;
+    for (int u = 0; u < ra.S; ++u) rank += key[u] > rows || (key[u] == rows && u < s);
+    order[rank] = (short)s;
+  }
+  __syncthreads();
+  return n;
+}
+
+// dW_gate = dA_g^T X_s and dW_up = dA_u^T X_s in one product: the A tile
+// interleaves 32-column blocks of dA_g and dA_u (RA / 2 intermediate rows of
+// both per tile); both operands read k-major, k = the slot's rows.
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_dw_gu(LayerPtrs<typename C::T> W,
+                                                        const typename C::T* __restrict__ X,
+                                                        const typename C::T* __restrict__ Xp,
+                                                        const typename C::T* __restrict__ dAg,
+                                                        const typename C::T* __restrict__ dAu, RowArgs ra,
+                                                        int accumulate) {
+  typedef typename C::T T;
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ short order[MAX_S + 1];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  constexpr int CI = C::RA / 2;
+  const int d = ra.d, I = ra.I, ld = ra.ldA;
+  const int MT = (I + CI - 1) / CI, NT = (d + C::RB - 1) / C::RB, tps = MT * NT;
+  const int total = __builtin_amdgcn_readfirstlane(tile_dw_order((FM_LDS int*)lds, order, ra, W.dwg)) * tps;
+  for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    const int s = __builtin_amdgcn_readfirstlane(order[t / tps]);
+    float* const dwg = ld_scalar(W.dwg + s);
+    float* const dwu = ld_scalar(W.dwu + s);
+    if (!dwu) continue;
+    int m, n;
+    band_order(t % tps, MT, NT, 8, m, n);
+    const SlotRows sr = slot_rows(s, ra.offsets, ra.S_r, ra.Tn, ra.k);
+    const int m0 = m * CI, n0 = n * C::RB;
+    const TileSrc<T> A{dAg + (size_t)sr.orow0 * ld + m0, dAu + (size_t)sr.orow0 * ld + m0, nullptr, ld, I - m0};
+    const TileSrc<T> B{(sr.shared ? X : Xp) + (size_t)sr.xrow0 * d + n0, nullptr, nullptr, d, d - n0};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, false, false, true, false>(A, B, sr.nrows, lds, acc);
+    tile_stage<C, float>(acc, lds);
+    Stage<float, C::RB>::template copy_rows<C::RA, 256>(
+        lds,
+        [=](int r) {
+          const int mm = m0 + 32 * (r >> 6) + (r & 31);
+          return mm < I ? ((r >> 5) & 1 ? dwu : dwg) + (size_t)mm * d + n0 : (float*)nullptr;
+        },
+        d - n0, accumulate);
+    barrier_lds();
+  }
+}
+
+// dW_down = dO^T H, both operands read k-major.
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_dw_d(LayerPtrs<typename C::T> W,
+                                                       const typename C::T* __restrict__ dO,
+                                                       const typename C::T* __restrict__ H, RowArgs ra,
+                                                       int accumulate) {
+  typedef typename C::T T;
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ short order[MAX_S + 1];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  const int d = ra.d, I = ra.I;
+  const int MT = (d + C::RA - 1) / C::RA, NT = (I + C::RB - 1) / C::RB, tps = MT * NT;
+  const int total = __builtin_amdgcn_readfirstlane(tile_dw_order((FM_LDS int*)lds, order, ra, W.dwg)) * tps;
+  for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    const int s = __builtin_amdgcn_readfirstlane(order[t / tps]);
+    float* const dwd = ld_scalar(W.dwd + s);
+    if (!dwd) continue;
+    int m, n;
+    band_order(t % tps, MT, NT, 8, m, n);
+    const SlotRows sr = slot_rows(s, ra.offsets, ra.S_r, ra.Tn, ra.k);
+    const int m0 = m * C::RA, n0 = n * C::RB;
+    const TileSrc<T> A{dO + (size_t)sr.orow0 * d + m0, nullptr, nullptr, d, d - m0};
+    const TileSrc<T> B{H + (size_t)sr.orow0 * I + n0, nullptr, nullptr, I, I - n0};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, false, false>(A, B, sr.nrows, lds, acc);
+    tile_stage<C, float>(acc, lds);
+    Stage<float, C::RB>::template copy_rows<C::RA, 256>(
+        lds, [=](int r) { return m0 + r < d ? dwd + (size_t)(m0 + r) * I + n0 : (float*)nullptr; }, I - n0, accumulate);
+    barrier_lds();
+  }
+}
+
+// ------------------------------------------------------------------ host ----
+
+// (Tile indices fit in 32 bits: a tile writes at least 16 KB of output, so 2^31
+// of them would not fit in memory.)
+// Blocks for at most `tiles` tiles, BPC per compute unit, a multiple of the XCDs.
+template <class C> dim3 tile_grid(long long tiles) {
+  const long long most = (long long)persistent_blocks() * C::BPC;
+  const long long g = (tiles + N_XCD - 1) / N_XCD * N_XCD;
+  return dim3((unsigned)(g < N_XCD ? N_XCD : g < most ? g : most));
+}
+// Upper bound of the row tiles of a layer (the bucket sizes are on the device).
+template <class C> long long max_row_tiles(const RowArgs& ra) {
+  const long long R = (long long)ra.Tn * ra.k;
+  const long long routed = R / C::RA + (R < ra.S_r ? R : ra.S_r);
+  return routed + (long long)(ra.S - ra.S_r) * ((ra.Tn + C::RA - 1) / C::RA);
+}
+
+using F64 = TileCfg<float, 64, 64, 2, 2, 1, 2, 4>;
+using F32 = TileCfg<float, 32, 64, 1, 2, 2, 4, 3>;
+using B32 = TileCfg<bf16, 32, 64, 1, 2, 2, 4, 3>;
+using B64 = TileCfg<bf16, 64, 128, 2, 2, 1, 3, 2>;
+using B128 = TileCfg<bf16, 128, 128, 2, 2, 1, 2, 2>;
+
+// Calls fn(C{}) with the tile of the plan's row products / weight gradients.
+template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
+  if (dtype == MOE_F32) {
+    if (p.rows == TilePlan::ROWS_32) fn(F32{});
+    else fn(F64{});
+  } else if (p.rows == TilePlan::ROWS_32) {
+    fn(B32{});
+  } else if (p.rows == TilePlan::ROWS_64) {
+    fn(B64{});
+  } else {
+    fn(B128{});
+  }
+}
+template <class Fn> void with_dw(const TilePlan& p, int dtype, Fn fn) {
+  if (dtype == MOE_F32) fn(F64{});
+  else if (p.dw == TilePlan::DW_64) fn(B64{});
+  else fn(B128{});
+}
+
+RowArgs row_args(const moe_layer* L, const int32_t* offsets, int T, int k, int ldA) {
+  return RowArgs{offsets, nullptr, L->S_routed, L->S_routed + L->S_shared, T, k, L->d, L->I, ldA};
+}
+
+}  // namespace
+
+// Persistent grid unit: one block per compute unit, a multiple of the XCD count.
+int persistent_blocks() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+    n = 256;
+  n = (n / N_XCD) * N_XCD;
+  return n < N_XCD ? N_XCD : n;
+}
+
+TilePlan tile_plan(const moe_layer* L, int T, int k) {
+  // r = average rows per slot; tiles estimated for average slots
+  const int S = L->S_routed + L->S_shared, n_sh = L->S_shared;
+  const double r = (double)T * (k + n_sh) / S;
+  const double active = (double)((long long)T * k < L->S_routed ? (long long)T * k : L->S_routed) + n_sh;
+  const long long wide = (2LL * L->I > L->d ? 2LL * L->I : L->d);
+  TilePlan p;
+  // Few rows: 32-row tiles (four waves splitting k two ways) make twice the
+  // blocks of the 64 x 128 tile and waste less on absent rows, which counts
+  // while those would not fill the chip twice.  fwd at T = 8: I = 688, d = 4096,
+  // 16 slots 36 against 49 us; I = 1408, d = 2048, 64 slots 83 against 93; at
+  // T = 64 (1408 tiles) 165 against 169, at r = 31 with 1452 tiles 283 against 249.
+  const bool few = r <= 32 && active * ((wide + 127) / 128) < 1024;
+  if (L->dtype == MOE_F32) {
+    // r = 7.5 (60 tokens, d = 712, I = 376, 32 slots): fwd 36 against 51 us
+    p.rows = few ? TilePlan::ROWS_32 : TilePlan::ROWS_64;
+    p.dw = TilePlan::DW_64;
+    return p;
+  }
+  // Row products, the sum of gate-up, down, dH and dX in us on 64 x 128, 128 x
+  // 128 and the large tiles (d = 2048, I = 1408, 64 slots unless said): r = 72
+  // 603, 604, 678; r = 96 678, 627, 699; r = 144 846, 751, 769; r = 192 980, 874,
+  // 855.  d = 4096, I = 688, 16 slots: r = 128 245, 285, 311; r = 194 333, 315,
+  // 347; r = 256 398, 334, 370; r = 512 628, 505, 461.  So the large tiles need
+  // slots of about 176 rows, or 288 where they would not fill the chip twice;
+  // 128-row tiles lose below about 88 rows and where they leave half of the
+  // 512 blocks idle.
+  const double mt128 = S * (r / 128 + 0.5), mt256 = S * (r / 256 + 0.5);
+  const double nt_gu = (L->I + 63) / 64, nt_gu256 = (L->I + 127) / 128;
+  if (few) p.rows = TilePlan::ROWS_32;
+  else if (r <= 88 || (r <= 176 && mt128 * nt_gu <= 288)) p.rows = TilePlan::ROWS_64;
+  else if (r <= 176 || (r <= 288 && mt256 * nt_gu256 < 512)) p.rows = TilePlan::ROWS_128;
+  else p.rows = TilePlan::LARGE_ROWS;
+  // Weight gradients (dW_down + dW_gate/up in us: 64 x 128, 128 x 128, large;
+  // every slot counted as tuning): their tiles number with the weights, not with
+  // the rows.  I = 256, d = 512, 16 slots: r = 512 48, 76, 108; r = 2048 146, 255,
+  // 322.  I = 512, d = 768, 32 slots: r = 512 134, 156, 170.  I = 1408, d = 2048,
+  // 64 slots: r = 72 347, 277, 293; r = 192 460, 370, 378; r = 288 -, 422, 415.  I =
+  // 688, d = 4096, 16 slots: r = 128 197, 177, 169; r = 512 411, 310, 295; r =
+  // 1024 -, 509, 428.
+  const double dw128 = (double)S * ((L->I + 63) / 64) * ((L->d + 127) / 128);
+  const double dw256 = (double)S * ((L->I + 127) / 128) * ((L->d + 255) / 256);
+  p.dw = r > 176 && dw256 >= 1024 ? TilePlan::LARGE_DW : dw128 >= 2048 ? TilePlan::DW_128 : TilePlan::DW_64;
+  return p;
+}
+
+int tile_norm_cols(const moe_layer* L, const TilePlan& p) {
+  int n = 0;
+  with_rows(p, L->dtype, [&](auto c) { n = decltype(c)::RB; });
+  return n;
+}
+
+void tile_fwd(const TilePlan& p, const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int Tn,
+              int k, void* Ag, void* Au, void* H, void* O, hipStream_t st) {
+  const RowArgs ra = row_args(L, offsets, Tn, k, L->I);
+  with_rows(p, L->dtype, [&](auto c) {
+    typedef decltype(c) C;
+    typedef typename C::T T;
+    const long long mt = max_row_tiles<C>(ra);
+    hipLaunchKernelGGL(kt_gate_up<C>, tile_grid<C>(mt * cdiv(ra.I, C::RB / 2)), dim3(256), 0, st, layer_ptrs<T>(L),
+                       (const T*)X, (const T*)Xp, ra, (T*)Ag, (T*)Au, (T*)H);
+    hipLaunchKernelGGL(kt_down<C>, tile_grid<C>(mt * cdiv(ra.d, C::RB)), dim3(256), 0, st, layer_ptrs<T>(L),
+                       (const T*)H, ra, (T*)O);
+  });
+}
+
+void tile_dh(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int Tn, int k, const void* Ag,
+             const void* Au, const void* dO, void* dAg, void* dAu, int ldA, float2* norms, hipStream_t st) {
+  const RowArgs ra = row_args(L, offsets, Tn, k, ldA);
+  with_rows(p, L->dtype, [&](auto c) {
+    typedef decltype(c) C;
+    typedef typename C::T T;
+    hipLaunchKernelGGL(kt_dh<C>, tile_grid<C>(max_row_tiles<C>(ra) * cdiv(ra.I, C::RB)), dim3(256), 0, st,
+                       layer_ptrs<T>(L), (const T*)dO, (const T*)Ag, (const T*)Au, ra, (T*)dAg, (T*)dAu, norms);
+  });
+}
+
+void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int Tn, int k, const void* dAg,
+             const void* dAu, int ldA, void* dXp, hipStream_t st) {
+  const RowArgs ra = row_args(L, offsets, Tn, k, ldA);
+  with_rows(p, L->dtype, [&](auto c) {
+    typedef decltype(c) C;
+    typedef typename C::T T;
+    hipLaunchKernelGGL(kt_dx<C>, tile_grid<C>(max_row_tiles<C>(ra) * cdiv(ra.d, C::RB)), dim3(256), 0, st,
+                       layer_ptrs<T>(L), (const T*)dAg, (const T*)dAu, ra, (T*)dXp);
+  });
+}
+
+void tile_dw(const TilePlan& p, const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int Tn,
+             int k, const void* H, const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate,
+             hipStream_t st) {
+  const RowArgs ra = row_args(L, offsets, Tn, k, ldA);
+  with_dw(p, L->dtype, [&](auto c) {
+    typedef decltype(c) C;
+    typedef typename C::T T;
+    hipLaunchKernelGGL(kt_dw_d<C>, tile_grid<C>((long long)ra.S * cdiv(ra.d, C::RA) * cdiv(ra.I, C::RB)), dim3(256), 0,
+                       st, layer_ptrs<T>(L), (const T*)dO, (const T*)H, ra, accumulate);
+    hipLaunchKernelGGL(kt_dw_gu<C>, tile_grid<C>((long long)ra.S * cdiv(ra.I, C::RA / 2) * cdiv(ra.d, C::RB)),
+                       dim3(256), 0, st, layer_ptrs<T>(L), (const T*)X, (const T*)Xp, (const T*)dAg, (const T*)dAu, ra,
+                       accumulate);
+  });
+}
+
+}  // namespace fm

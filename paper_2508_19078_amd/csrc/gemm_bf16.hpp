@@ -46,13 +46,34 @@
 
 #include <type_traits>
 
-#include "gemm.hpp"
+#include "common.hpp"
 
 namespace fm {
 
 #define FM_LDS __attribute__((address_space(3)))
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+// Output coordinates of four accumulator values: a row and the first of four
+// consecutive columns of the block tile.
+struct AccCoord {
+  int row, col4;
+};
+
+// 4 consecutive values <-> global memory of T.
+__device__ __forceinline__ void store4(bf16* p, f32x4_t v) {
+  u32x2_t o;
+  o[0] = pk_bf16(v[0], v[1]);
+  o[1] = pk_bf16(v[2], v[3]);
+  *(FM_GLOBAL u32x2_t*)(p) = o;
+}
+__device__ __forceinline__ void store4(float* p, f32x4_t v) { *(FM_GLOBAL f32x4_t*)(p) = v; }
+__device__ __forceinline__ f32x4_t load4(const bf16* p) {
+  const u32x2_t w = *(const FM_GLOBAL u32x2_t*)(p);
+  return f32x4_t{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xFFFF0000u),
+                 __uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xFFFF0000u)};
+}
+__device__ __forceinline__ f32x4_t load4(const float* p) { return *(const FM_GLOBAL f32x4_t*)(p); }
 
 // Tile configuration: RA x RB block tile, WM x WN waves, BK k per slab,
 // separate LDS rings of NSA slabs for A and NSB slabs for B (NSA = NSB + 1: the
@@ -452,7 +473,7 @@ template <typename T, int COLS> struct Stage {
   static constexpr int EPC = 16 / sizeof(T);         // elements per 16-byte chunk
   static constexpr int CPR = COLS / EPC;             // chunks per row
   static constexpr int ROW_BYTES = COLS * (int)sizeof(T);
-  static_assert(CPR == 16 || CPR == 32 || CPR == 64, "chunks per row");
+  static_assert(CPR >= 4 && CPR <= 64 && (CPR & (CPR - 1)) == 0, "chunks per row");
 
   // LDS byte offset of the 4 values at (row, col), col a multiple of 4.
   static __device__ __forceinline__ uint32_t at(int row, int col) {

@@ -1,0 +1,321 @@
+// Small-tile MFMA core for the grouped expert FFN (gfx950, wave64): blocks of
+// 4 waves, several per compute unit, fp32 or bf16.
+//
+// A block computes an RA x RB tile of C = sum_k A(r, k) B(n, k); its waves
+// form a WM x WN (x WK) grid and each owns MI x NJ 32 x 32 MFMA tiles
+// (v_mfma_f32_32x32x16_bf16, or 4 x v_mfma_f32_32x32x2_f32 per 8 k), operands
+// swapped so that a lane holds groups of four consecutive output columns.
+//
+// * Slabs of 128 bytes of k per row (64 bf16 or 32 fp32) go global -> LDS with
+//   global_load_lds_dwordx4 into a ring of NS slabs of both operands, NS - 1 of
+//   them in flight; one block barrier per slab.  The other blocks of the
+//   compute unit fill the matrix pipe over a block's barriers, its first slabs
+//   and its epilogue, so nothing is pipelined across tiles.
+// * K-contiguous operands (element (r, k) at p[r * ld + k]) are stored as
+//   [R][128 B], the 16-byte chunk index XOR-swizzled by (r >> 1) & 7: sixteen
+//   consecutive rows read at one logical chunk cover the 64 banks once.  A DMA
+//   instruction moves whole 128-byte lines of 8 rows.
+// * MN-contiguous operands (element (r, k) at p[k * ld + r]) are stored as
+//   R / 32 column blocks of k-rows.  bf16: [64 k][32 r], read with
+//   ds_read_b64_tr_b16.  fp32: [32 k][32 r], k-rows of each group of 8 in the
+//   order 0 4 1 5 2 6 3 7, so that the two halves of a wave (k and k + 4) read
+//   the two halves of the banks.
+// * An operand may interleave two matrices in 32-row blocks (gate and up), and
+//   two products may be summed as one k loop (the slabs of the second pair
+//   follow those of the first: dX = dA_g W_gate + dA_u W_up).
+// * Rows past the operand's extent read a clamped (valid) address and feed
+//   outputs that are never stored; k past K is clamped too and both operands'
+//   slabs are zeroed there before they are read.
+#pragma once
+
+#include "gemm_bf16.hpp"
+
+namespace fm {
+
+// WM x WN x WK waves (WK: the waves that split each slab's k), NS slabs in the
+// ring, BPC blocks per compute unit (what the ring leaves room for).
+template <typename T_, int RA_, int RB_, int WM_, int WN_, int WK_, int NS_, int BPC_> struct TileCfg {
+  typedef T_ T;
+  static constexpr int RA = RA_, RB = RB_, WM = WM_, WN = WN_, WK = WK_, NS = NS_, BPC = BPC_;
+  static constexpr int THREADS = 256;
+  static constexpr int V = 16 / (int)sizeof(T);       // elements per 16 bytes
+  static constexpr int BK = 8 * V;                    // k per slab (128 bytes)
+  static constexpr int KS = 4;                        // MFMA steps per slab
+  static constexpr int TM = RA / WM, TN = RB / WN;    // wave sub-tile
+  static constexpr int MI = TM / 32, NJ = TN / 32;    // MFMA tiles per wave
+  static constexpr int A_BYTES = RA * 128, SLAB = (RA + RB) * 128;
+  static constexpr int A_INS = RA / 32, B_INS = RB / 32;   // DMA instructions per wave and slab
+  static constexpr int INS = A_INS + B_INS;
+  static constexpr int LDS = NS * SLAB;
+  static_assert(WM * WN * WK == 4 && TM % 32 == 0 && TN % 32 == 0, "4 waves of 32-multiples");
+  static_assert(NS >= 2 && BPC * (LDS + 6 * 1024) <= 160 * 1024 + 5 * 1024 && (NS - 2) * INS < 64, "ring");
+  static_assert(WK == 1 || (WK - 1) * RA * RB * 4 <= LDS, "partial sums");
+};
+
+// One operand, relative to the tile origin.  p2: the second matrix of an
+// interleaved pair (blocks of 32 logical rows alternate); pk: the matrix of the
+// second product of a two-product loop.  rows = valid physical rows.
+template <typename T> struct TileSrc {
+  const T* p;
+  const T* p2;
+  const T* pk;
+  int ld;
+  int rows;
+};
+
+template <typename T, bool KC, int R, bool INTER> struct TileDma {
+  static constexpr int V = 16 / (int)sizeof(T), BK = 8 * V;
+  static constexpr int NI = R / 32;      // instructions per wave and slab
+  static constexpr int CB = R / 32;      // column blocks (MN)
+  static constexpr int NB = INTER ? NI : 1;
+  uint32_t off[NI];
+  uintptr_t base[NB];   // uniform: the matrix of each instruction at the next slab
+  uintptr_t step;
+  int ins0;             // this wave's first instruction
+
+  __device__ __forceinline__ static int block_of(int ins) { return KC ? ins >> 2 : ins % CB; }   // 32-row block
+  __device__ __forceinline__ static int lds_at(int ins) {
+    return KC ? ins * 1024 : (ins % CB) * 4096 + (ins / CB) * 1024;
+  }
+  // Byte offset (from the matrix of the instruction's block at the slab's first
+  // k) of this lane's 16 bytes; kv = valid k from there on.
+  __device__ __forceinline__ static uint32_t lane_off(const TileSrc<T>& s, int ins, int lane, int kv) {
+    if (KC) {
+      const int r = 8 * ins + (lane >> 3);
+      const int k = V * ((lane & 7) ^ ((r >> 1) & 7));
+      const int pr = INTER ? 32 * (r >> 6) + (r & 31) : r;
+      return (uint32_t)(((size_t)min(pr, s.rows - 1) * s.ld + min(k, kv - V)) * sizeof(T));
+    }
+    const int blk = ins % CB, kg = ins / CB;
+    const int r0 = 32 * (INTER ? blk >> 1 : blk);
+    int k, r;
+    if (sizeof(T) == 2) {
+      k = 16 * kg + (lane >> 2);
+      r = r0 + 8 * (lane & 3);
+    } else {
+      k = 8 * kg + ((lane >> 4) & 3) + 4 * ((lane >> 3) & 1);
+      r = r0 + 4 * (lane & 7);
+    }
+    return (uint32_t)(((size_t)min(k, kv - 1) * s.ld + min(r, s.rows - V)) * sizeof(T));
+  }
+  __device__ __forceinline__ void rebase(const TileSrc<T>& s, bool second) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      base[u] = (uintptr_t)(second ? s.pk : s.p);
+      if (INTER) base[u] += (block_of(ins0 + u) & 1) ? (uintptr_t)s.p2 - (uintptr_t)s.p : 0;
+    }
+  }
+  __device__ __forceinline__ void init(const TileSrc<T>& s) {
+    const int lane = lane_id();
+    ins0 = wave_id() * NI;
+    step = KC ? 128 : (uintptr_t)BK * s.ld * sizeof(T);
+#pragma unroll
+    for (int u = 0; u < NI; ++u) off[u] = lane_off(s, ins0 + u, lane, BK);
+    rebase(s, false);
+  }
+  // Issues the next slab, kv valid k, and advances.
+  __device__ __forceinline__ void issue(const TileSrc<T>& s, int kv, FM_LDS char* tile) {
+    if (kv >= BK) {
+#pragma unroll
+      for (int u = 0; u < NI; ++u) dma16s((const void*)base[INTER ? u : 0], off[u], tile + lds_at(ins0 + u));
+    } else {
+      const int lane = lane_id_here();
+#pragma unroll
+      for (int u = 0; u < NI; ++u)
+        dma16s((const void*)base[INTER ? u : 0], lane_off(s, ins0 + u, lane, kv), tile + lds_at(ins0 + u));
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) base[u] += step;
+  }
+  // Zeroes the slab's k >= kv in LDS (the block's 256 threads; after the slab has landed).
+  __device__ __forceinline__ static void zero_tail(int kv, FM_LDS char* tile) {
+    for (int c = threadIdx.x; c < R * 8; c += 256) {   // 16-byte chunks
+      int k;
+      if (KC) k = V * ((c & 7) ^ ((c >> 4) & 7));      // row c / 8
+      else if (sizeof(T) == 2) k = (c >> 2) & 63;      // 64-byte k-rows
+      else k = 8 * ((c >> 6) & 3) + ((c >> 4) & 3) + 4 * ((c >> 3) & 1);   // 128-byte k-rows, permuted in groups of 8
+      if (k >= kv) *(FM_LDS u32x4_t*)(tile + 16 * c) = u32x4_t{0, 0, 0, 0};
+    }
+  }
+};
+
+template <typename T> struct tile_frag;
+template <> struct tile_frag<bf16> { typedef bf16x8_t type; };
+template <> struct tile_frag<float> { typedef f32x4_t type; };
+
+// MFMA fragments: lane l holds row r0 + l % 32 and k KST * step +
+// (KST / 2) (l / 32) + 0 .. KST / 2 - 1 (16 bytes) of each 32-row block.
+template <typename T, bool KC, int R, int NB> struct TileFrag {
+  typedef typename tile_frag<T>::type frag;
+  uint32_t off[NB];
+
+  __device__ __forceinline__ void init(int row0) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int r0 = row0 + 32 * i;
+      if (KC) {
+        const int r = r0 + (lane & 31);
+        off[i] = (uint32_t)(r * 128 + (((lane >> 5) ^ ((r >> 1) & 7)) << 4));
+      } else if (sizeof(T) == 2) {
+        // as B16Frag: output lane i, element j of a 16-lane group comes from
+        // the address of lane 4 j + i / 4, offset i % 4
+        const int g = lane >> 4, L = lane & 15;
+        off[i] = (uint32_t)((r0 >> 5) * 4096 + (8 * (g >> 1) + (L >> 2)) * 64 + (16 * (g & 1) + 4 * (L & 3)) * 2);
+      } else {
+        off[i] = (uint32_t)((r0 >> 5) * 4096 + (lane >> 5) * 128 + (lane & 31) * 4);
+      }
+    }
+  }
+  __device__ __forceinline__ frag read(const FM_LDS char* tile, int i, int st) const {
+    if constexpr (KC) {
+      return __builtin_bit_cast(frag, *(const FM_LDS u32x4_t*)(tile + (off[i] ^ (uint32_t)(st << 5))));
+    } else if constexpr (sizeof(T) == 2) {
+      const FM_LDS char* p = tile + off[i] + st * 1024;
+      const i16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FM_LDS i16x4_t*)p);
+      const i16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FM_LDS i16x4_t*)(p + 4 * 64));
+      const u32x2_t w0 = __builtin_bit_cast(u32x2_t, v0), w1 = __builtin_bit_cast(u32x2_t, v1);
+      return __builtin_bit_cast(frag, u32x4_t{w0[0], w0[1], w1[0], w1[1]});
+    } else {
+      const FM_LDS char* p = tile + off[i] + st * 1024;
+      frag f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = *(const FM_LDS float*)(p + 256 * e);
+      return f;
+    }
+  }
+};
+
+__device__ __forceinline__ f32x16_t tile_mma(bf16x8_t b, bf16x8_t a, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t tile_mma(f32x4_t b, f32x4_t a, f32x16_t c) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(b[i], a[i], c, 0, 0, 0);
+  return c;
+}
+
+// The wave's LDS reads are done and the block meets.
+__device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Waits until at most min(after, N) slabs of INS instructions are in flight.
+template <int N, int INS> __device__ __forceinline__ void tile_wait(int after) {
+  if constexpr (N == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (after >= N) wait_vmcnt<N * INS>();
+    else tile_wait<N - 1, INS>(after);
+  }
+}
+
+// acc += A B^T over [0, K) (and over [0, K) of the second pair with TWO).  The
+// LDS must be free on entry and is free on return (a barrier ends the call).
+// Slab kt has landed once at most the NS - 2 slabs issued after it are in
+// flight; the barrier at the top of slab kt says that every wave has read slab
+// kt - 1, whose buffer then takes slab kt + NS - 1.  A wave issues all of a
+// slab's fragment reads, then the DMA of the coming slab (its address work
+// covers the first reads' latency), then the MFMAs.  The partial last slab is
+// zero-filled in LDS, so that one copy of the MFMA code serves all slabs.
+template <class C, bool AKC, bool BKC, bool AI = false, bool BI = false, bool TWO = false>
+__device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const TileSrc<typename C::T>& B, int K,
+                                          FM_LDS char* lds, B16Acc<C::MI, C::NJ>& acc) {
+  typedef typename C::T T;
+  typedef typename tile_frag<T>::type frag;
+  const int n1 = (K + C::BK - 1) / C::BK;
+  const int nk = TWO ? 2 * n1 : n1;
+  if (nk == 0) {   // no rows: the accumulators stay zero
+    tile_barrier();
+    return;
+  }
+  const int wave = wave_id();
+  TileDma<T, AKC, C::RA, AI> da;
+  TileDma<T, BKC, C::RB, BI> db;
+  da.init(A);
+  db.init(B);
+  TileFrag<T, AKC, C::RA, C::MI> fa;
+  TileFrag<T, BKC, C::RB, C::NJ> fb;
+  fa.init((wave % C::WM) * C::TM);
+  fb.init((wave / C::WM % C::WN) * C::TN);
+  constexpr int KW = C::KS / C::WK;   // steps per wave and slab
+  const int st0 = wave / (C::WM * C::WN) * KW;
+  auto issue = [&](int s, int buf) {
+    if (TWO && s == n1) {
+      da.rebase(A, true);
+      db.rebase(B, true);
+    }
+    const int kv = K - (TWO && s >= n1 ? s - n1 : s) * C::BK;
+    FM_LDS char* t = lds + buf * C::SLAB;
+    da.issue(A, kv, t);
+    db.issue(B, kv, t + C::A_BYTES);
+  };
+#pragma nounroll
+  for (int s = 0; s < C::NS - 1 && s < nk; ++s) issue(s, s);
+  int cur = 0, nxt = C::NS - 1;   // buffers of slab kt and of slab kt + NS - 1
+#pragma nounroll
+  for (int kt = 0; kt < nk; ++kt) {
+    const int after = nk - 1 - kt;   // slabs after kt
+    tile_wait<C::NS - 2, C::INS>(after);
+    tile_barrier();
+    FM_LDS char* const ta = lds + cur * C::SLAB;
+    FM_LDS char* const tb = ta + C::A_BYTES;
+    const int kv = K - (TWO && kt >= n1 ? kt - n1 : kt) * C::BK;
+    if (kv < C::BK) {
+      da.zero_tail(kv, ta);
+      db.zero_tail(kv, tb);
+      tile_barrier();
+    }
+    frag xa[KW][C::MI], xb[KW][C::NJ];
+#pragma unroll
+    for (int st = 0; st < KW; ++st) {
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i) xa[st][i] = fa.read(ta, i, st0 + st);
+#pragma unroll
+      for (int j = 0; j < C::NJ; ++j) xb[st][j] = fb.read(tb, j, st0 + st);
+    }
+    sched_fence();
+    if (kt + C::NS - 1 < nk) issue(kt + C::NS - 1, nxt);
+    sched_fence();
+#pragma unroll
+    for (int st = 0; st < KW; ++st)
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NJ; ++j) acc.v[i][j] = tile_mma(xb[st][j], xa[st][i], acc.v[i][j]);
+    cur = cur + 1 == C::NS ? 0 : cur + 1;
+    nxt = nxt + 1 == C::NS ? 0 : nxt + 1;
+  }
+  tile_barrier();
+  if (C::WK > 1) {
+    // wave wk > 0 leaves its sums at [wk - 1][wave of the WM x WN grid][tile][quad][lane]
+    const int w = wave % (C::WM * C::WN), wk = wave / (C::WM * C::WN);
+    const int lane = lane_id_here();
+    auto at = [&](int k, int i, int j, int q) {
+      return lds + (((((k - 1) * C::WM * C::WN + w) * C::MI + i) * C::NJ + j) * 4 + q) * 1024 + lane * 16;
+    };
+    if (wk > 0) {
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) *(FM_LDS f32x4_t*)at(wk, i, j, q) = acc.quad(i, j, q);
+    }
+    tile_barrier();
+    if (wk == 0) {
+      for (int k = 1; k < C::WK; ++k)
+#pragma unroll
+        for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+          for (int j = 0; j < C::NJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const f32x4_t v = *(const FM_LDS f32x4_t*)at(k, i, j, q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc.v[i][j][4 * q + e] += v[e];
+            }
+    }
+    tile_barrier();
+  }
+}
+
+}  // namespace fm

@@ -25,7 +25,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 # The kernels of moe_grouped_swiglu_fwd + moe_grouped_swiglu_bwd (bf16 path).
 FFN_KERNELS = ("k_build_sched", "kb_gate_up", "kb_down", "kb_dh", "kb_dx", "kb_dw_gu", "kb_dw_d")
 # Sources those kernels are built from.
-FFN_SOURCES = ("csrc/ffn.hip", "csrc/gemm_bf16.hpp", "csrc/gemm.hpp", "csrc/common.hpp")
+FFN_SOURCES = ("csrc/ffn.hip", "csrc/ffn_common.hpp", "csrc/gemm_bf16.hpp", "csrc/common.hpp")
 CALIB_KERNEL = "copyBuffer"
 
 

@@ -1,0 +1,77 @@
+"""The grouped FFN at the sizes where its tile shapes change: each small tile
+(32, 64 and 128 rows), the large one, and both ways to pair them with the
+weight gradients' tiles, at row, column and k remainders (d and I multiples of
+8, a single token, empty tuning slots, shared experts).  A whole step through
+the C ABI against the fp64 oracle on the oracle's routing."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2508_19078_amd import api, workloads as W
+from paper_2508_19078_amd.layer import LayerInputs, MoELayerRunner
+
+from gpu_harness import TOL_FFN, OracleLayer, host, log, rel_fro
+
+pytestmark = pytest.mark.gpu
+
+# fp32: three chained products of at most 1032 terms, each with a rounding error
+# of about sqrt(1032) 2^-24 = 2e-6 relative to its norm
+TOL_F32 = 1e-5
+
+
+def _w(T, d, E, k, I, dtype="bf16", ns=0, bias="normal"):
+    return W.LayerWorkload(name=f"tiles_{dtype}_{T}_{d}_{E}_{k}_{I}_{ns}", cid=700 + T % 97, T=T, d=d, E=E, k=k, I=I,
+                           dtype=dtype, n_shared=ns, bias_kind=bias, bias_var=1.0, zipf_s=1.2)
+
+
+# r = T (k + shared) / slots decides the row tile, the weights' size the dW tile
+CASES = [
+    _w(1, 72, 4, 2, 40),                       # one token, two empty slots: 32-row tile, one slab with a remainder
+    _w(33, 200, 6, 2, 136, ns=1),              # r = 14
+    _w(130, 264, 8, 4, 136),                   # r = 65: 64-row tile
+    _w(150, 136, 4, 2, 24, ns=1),              # r = 90 but few tiles: 64-row tile
+    _w(800, 1032, 64, 8, 264),                 # r = 100: 128-row tile, 128-row dW tile
+    _w(1600, 520, 64, 8, 776, bias="zipf"),    # r = 200: large dW tile
+    _w(700, 136, 4, 2, 72),                    # r = 350: large tile, 64-row dW tile
+    _w(2, 40, 4, 1, 24, "f32"),                # fp32, empty slots, k below one slab
+    _w(40, 136, 8, 4, 72, "f32", ns=1),        # r = 22: 32-row tile
+    _w(300, 1032, 5, 3, 264, "f32", bias="zipf"),   # r = 180: 64-row tile
+]
+
+
+@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
+def test_step(w):
+    inp = LayerInputs(w)
+    ref = OracleLayer(w, inp)
+    r = MoELayerRunner(w, inp)
+    r.profile()
+    r.merge(counts=torch.from_numpy(ref.counts.astype(np.int32)).cuda())
+    log(w.name)
+    r.forward(idx=torch.from_numpy(ref.idx.astype(np.int32)).cuda(),
+              gate=torch.from_numpy(ref.gate.astype(np.float32)).cuda())
+    r.backward(dgate=True)
+    u = torch.empty(r.S_r + w.n_shared, dtype=torch.float32, device="cuda")
+    api.moe_expert_utility(r.layer_tables, r.x_sq, r.dy_sq, r.perm_token, r.perm_gate, r.offsets, w.T, w.k, r.ws_bwd, u)
+    torch.cuda.synchronize()
+    tol = TOL_F32 if w.dtype == "f32" else TOL_FFN
+    dX, dW, dgate = ref.backward()
+    assert rel_fro(host(r.Y), ref.forward()) <= tol
+    assert rel_fro(host(r.dX), dX) <= tol
+    assert rel_fro(host(r.dgate), dgate) <= tol
+    assert rel_fro(host(u), O.expert_utility_rank_one(ref.X, ref.dY, ref.idx, ref.gate, ref.plan.expert_map,
+                                                      ref.slots)) <= tol
+    once = []
+    for i, s in enumerate(r.tuning_slots):
+        got = [host(t[i]).copy() for t in (r.dWg, r.dWu, r.dWd)]
+        once.append(got)
+        for a, b in zip(got, dW[s]):
+            if not np.any(b):
+                assert not a.any()               # an empty tuning slot: exact zeros
+            else:
+                assert rel_fro(a, b) <= tol
+    r.backward(accumulate_dw=True)               # the same step again: fp32 x + x
+    torch.cuda.synchronize()
+    for i, got in enumerate(once):
+        for a, t in zip(got, (r.dWg, r.dWu, r.dWd)):
+            np.testing.assert_array_equal(host(t[i]), 2 * a)
