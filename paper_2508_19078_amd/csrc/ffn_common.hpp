@@ -54,6 +54,23 @@ template <typename T> LayerPtrs<T> layer_ptrs(const moe_layer* L) {
                       L->dw_gate, L->dw_up, L->dw_down};
 }
 
+// Codes and row scales of the int8 forward.
+struct Q8Ptrs {
+  const int8_t* const* qg;
+  const int8_t* const* qu;
+  const int8_t* const* qd;
+  const float* const* sg;
+  const float* const* su;
+  const float* const* sd;
+};
+
+// Four consecutive row scales from col (clamped so that the four stay inside
+// the row count n, n >= 4; columns past n are never stored).
+__device__ __forceinline__ f32x4_t scale4(const float* s, int col, int n) {
+  const int c = min(col, n - 4);
+  return f32x4_t{s[c], s[c + 1], s[c + 2], s[c + 3]};
+}
+
 __device__ __forceinline__ float sigm(float z) { return 1.0f / (1.0f + expf(-z)); }
 // Logistic function with the hardware exp2 and reciprocal (about 1 ulp each),
 // for epilogues whose results are rounded to bf16.

@@ -437,6 +437,96 @@ __global__ __launch_bounds__(256, C::BPC) void kt_dw_d(LayerPtrs<typename C::T> 
   }
 }
 
+// The int8 forward: H = silu(s_g (X_s Q_g^T)) (s_u (X_s Q_u^T)) with the codes
+// interleaved as in kt_gate_up.  A wave's columns are whole gate / up pairs of
+// 32-blocks, so H is formed from its fp32 sums in registers.
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_q8_gate_up(Q8Ptrs W, const bf16* __restrict__ X,
+                                                             const bf16* __restrict__ Xp, RowArgs ra,
+                                                             bf16* __restrict__ H) {
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ int pre[MAX_S + 1];
+  __shared__ int wsum[4];
+  static_assert(C::NJ % 2 == 0, "gate / up pairs per wave");
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  constexpr int CI = C::RB / 2;
+  using SG = Stage<bf16, CI>;
+  const int d = ra.d, I = ra.I, NT = (I + CI - 1) / CI;
+  tile_sched(pre, wsum, ra, C::RA);
+  const Span sp = row_span(pre, ra, NT);
+  for (int t = sp.lo; t < sp.hi; t += sp.step) {
+    const RowTile r = row_tile_at(pre, ra, t, NT, C::RA);
+    const int n0 = r.n * CI, cols = I - n0;
+    const TileSrc<bf16> A{(r.sr.shared ? X : Xp) + (size_t)(r.sr.xrow0 + r.m0) * d, nullptr, nullptr, d, r.rows};
+    const TileSrc<int8_t> B{ld_scalar(W.qg + r.s) + (size_t)n0 * d, ld_scalar(W.qu + r.s) + (size_t)n0 * d, nullptr, d,
+                            cols};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, true, true, false, true>(A, B, d, lds, acc);
+    if (tile_holds<C>()) {
+      const float* const sg = ld_scalar(W.sg + r.s) + n0;
+      const float* const su = ld_scalar(W.su + r.s) + n0;
+#pragma unroll
+      for (int jj = 0; jj < C::NJ / 2; ++jj)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c4 = tile_coord<C>(0, 2 * jj, q).col4, col = 32 * (c4 >> 6) + (c4 & 31);
+          const f32x4_t cg = scale4(sg, col, cols), cu = scale4(su, col, cols);
+#pragma unroll
+          for (int i = 0; i < C::MI; ++i) {
+            const f32x4_t g = acc.quad(i, 2 * jj, q), u = acc.quad(i, 2 * jj + 1, q);
+            f32x4_t h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float a = g[e] * cg[e];
+              h[e] = a * sigm_fast(a) * (u[e] * cu[e]);
+            }
+            SG::put4(lds, tile_coord<C>(i, 2 * jj, q).row, col, h);
+          }
+        }
+    }
+    barrier_lds_writes();
+    SG::template copy_out<C::RA, 256>(lds, H + r.ob * I + n0, I, r.rows, cols);
+    barrier_lds();
+  }
+}
+
+// O = s_d (H Q_d^T).
+template <class C>
+__global__ __launch_bounds__(256, C::BPC) void kt_q8_down(Q8Ptrs W, const bf16* __restrict__ H, RowArgs ra,
+                                                          bf16* __restrict__ O) {
+  __shared__ __align__(16) char lds_[C::LDS];
+  __shared__ int pre[MAX_S + 1];
+  __shared__ int wsum[4];
+  FM_LDS char* const lds = (FM_LDS char*)lds_;
+  const int d = ra.d, I = ra.I, NT = (d + C::RB - 1) / C::RB;
+  tile_sched(pre, wsum, ra, C::RA);
+  const Span sp = row_span(pre, ra, NT);
+  for (int t = sp.lo; t < sp.hi; t += sp.step) {
+    const RowTile r = row_tile_at(pre, ra, t, NT, C::RA);
+    const int n0 = r.n * C::RB, cols = d - n0;
+    const TileSrc<bf16> A{H + r.ob * I, nullptr, nullptr, I, r.rows};
+    const TileSrc<int8_t> B{ld_scalar(W.qd + r.s) + (size_t)n0 * I, nullptr, nullptr, I, cols};
+    B16Acc<C::MI, C::NJ> acc;
+    acc.zero();
+    tile_gemm<C, true, true>(A, B, I, lds, acc);
+    const float* const sd = ld_scalar(W.sd + r.s) + n0;
+#pragma unroll
+    for (int j = 0; j < C::NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4_t c4 = scale4(sd, tile_coord<C>(0, j, q).col4, cols);
+#pragma unroll
+        for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc.v[i][j][4 * q + e] *= c4[e];
+      }
+    tile_stage<C, bf16>(acc, lds);
+    Stage<bf16, C::RB>::template copy_out<C::RA, 256>(lds, O + r.ob * d + n0, d, r.rows, cols);
+    barrier_lds();
+  }
+}
+
 // ------------------------------------------------------------------ host ----
 
 // (Tile indices fit in 32 bits: a tile writes at least 16 KB of output, so 2^31
@@ -459,6 +549,13 @@ using F32 = TileCfg<float, 32, 64, 1, 2, 2, 4, 3>;
 using B32 = TileCfg<bf16, 32, 64, 1, 2, 2, 4, 3>;
 using B64 = TileCfg<bf16, 64, 128, 2, 2, 1, 3, 2>;
 using B128 = TileCfg<bf16, 128, 128, 2, 2, 1, 2, 2>;
+
+// int8 weights.  Widening a fragment costs 12 vector instructions, so a wave
+// covers all of the tile's rows (each code is widened once per wave, not once
+// per row of waves): 2 or 4 MFMAs per widened fragment on the 64 and 128-row tiles.
+using Q32 = TileCfg<bf16, 32, 128, 1, 2, 2, 4, 3, 1>;
+using Q64 = TileCfg<bf16, 64, 128, 1, 2, 2, 3, 3, 1>;
+using Q128 = TileCfg<bf16, 128, 256, 1, 4, 1, 2, 2, 1>;
 
 // Calls fn(C{}) with the tile of the plan's row products / weight gradients.
 template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
@@ -596,6 +693,43 @@ void tile_dw(const TilePlan& p, const moe_layer* L, const void* X, const void* X
                        dim3(256), 0, st, layer_ptrs<T>(L), (const T*)X, (const T*)Xp, (const T*)dAg, (const T*)dAu, ra,
                        accumulate);
   });
+}
+
+// The int8 forward's tile, from the average rows per slot r and the tiles (time
+// of gate-up + down in us on the 32, 64 and 128-row tile; in brackets the
+// 256-row, 8-wave tile the int8 forward used before, with the same widening).
+// d = 2048, I = 1408, 64 slots: r = 6 96, 93, 121 [179]; r = 24 142, 135, 156
+// [233]; r = 48 190, 162, 185 [252]; r = 96 274, 225, 218 [319]; r = 384 925, 659,
+// 526 [575]; r = 768 1728, 1218, 912 [966].  d = 4096, I = 688, 16 slots: r = 2 48,
+// 54, 92 [106]; r = 64 65, 69, 99 [116]; r = 194 (192 128-row tiles) 133, 104, 125
+// [149]; r = 375 (330 tiles) 242, 170, 162 [191]; r = 1024 623, 429, 358 [369].  d =
+// 768, I = 512, 32 slots: r = 2 20, 23, 34 [43]; r = 128 40, 33, 38 [60]; r = 512
+// 107, 77, 68 [93].
+int q8_tile(const moe_layer_q8* L, int T, int k) {
+  const int S = L->S_routed + L->S_shared;
+  const double r = (double)T * (k + L->S_shared) / S;
+  const double active = (double)((long long)T * k < L->S_routed ? (long long)T * k : L->S_routed) + L->S_shared;
+  if (r <= 64 && active * ((2LL * L->I + 127) / 128) < 768) return 32;
+  return r >= 72 && S * (r / 128 + 0.5) * ((L->I + 127) / 128) >= 288 ? 128 : 64;
+}
+
+void tile_fwd_q8(const moe_layer_q8* L, const void* X, const void* Xp, const int32_t* offsets, int Tn, int k, void* H,
+                 void* O, hipStream_t st) {
+  const RowArgs ra{offsets, nullptr, L->S_routed, L->S_routed + L->S_shared, Tn, k, L->d, L->I, L->I};
+  const Q8Ptrs W{L->q_gate, L->q_up, L->q_down, L->s_gate, L->s_up, L->s_down};
+  auto run = [&](auto c) {
+    typedef decltype(c) C;
+    const long long mt = max_row_tiles<C>(ra);
+    hipLaunchKernelGGL(kt_q8_gate_up<C>, tile_grid<C>(mt * cdiv(ra.I, C::RB / 2)), dim3(256), 0, st, W, (const bf16*)X,
+                       (const bf16*)Xp, ra, (bf16*)H);
+    hipLaunchKernelGGL(kt_q8_down<C>, tile_grid<C>(mt * cdiv(ra.d, C::RB)), dim3(256), 0, st, W, (const bf16*)H, ra,
+                       (bf16*)O);
+  };
+  switch (q8_tile(L, Tn, k)) {
+    case 32: run(Q32{}); break;
+    case 64: run(Q64{}); break;
+    default: run(Q128{}); break;
+  }
 }
 
 }  // namespace fm

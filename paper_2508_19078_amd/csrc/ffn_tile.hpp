@@ -26,6 +26,10 @@ void tile_dw(const TilePlan& p, const moe_layer* L, const void* X, const void* X
 void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int T, int k, const void* dAg,
              const void* dAu, int ldA, void* dXp, hipStream_t st);
 
+// The int8 forward.
+void tile_fwd_q8(const moe_layer_q8* L, const void* X, const void* Xp, const int32_t* offsets, int T, int k, void* H,
+                 void* O, hipStream_t st);
+
 // One block per compute unit, rounded to the XCD count.
 int persistent_blocks();
 

@@ -34,17 +34,21 @@ namespace fm {
 
 // WM x WN x WK waves (WK: the waves that split each slab's k), NS slabs in the
 // ring, BPC blocks per compute unit (what the ring leaves room for).
-template <typename T_, int RA_, int RB_, int WM_, int WN_, int WK_, int NS_, int BPC_> struct TileCfg {
+// BE: bytes per B element, sizeof(T) or 1 (int8 codes widened exactly to bf16 as
+// fragments are read; K-contiguous, 64-byte slab rows).
+template <typename T_, int RA_, int RB_, int WM_, int WN_, int WK_, int NS_, int BPC_, int BE_ = (int)sizeof(T_)>
+struct TileCfg {
   typedef T_ T;
-  static constexpr int RA = RA_, RB = RB_, WM = WM_, WN = WN_, WK = WK_, NS = NS_, BPC = BPC_;
+  typedef std::conditional_t<BE_ == 1, int8_t, T_> TB;
+  static constexpr int RA = RA_, RB = RB_, WM = WM_, WN = WN_, WK = WK_, NS = NS_, BPC = BPC_, BE = BE_;
   static constexpr int THREADS = 256;
   static constexpr int V = 16 / (int)sizeof(T);       // elements per 16 bytes
   static constexpr int BK = 8 * V;                    // k per slab (128 bytes)
   static constexpr int KS = 4;                        // MFMA steps per slab
   static constexpr int TM = RA / WM, TN = RB / WN;    // wave sub-tile
   static constexpr int MI = TM / 32, NJ = TN / 32;    // MFMA tiles per wave
-  static constexpr int A_BYTES = RA * 128, SLAB = (RA + RB) * 128;
-  static constexpr int A_INS = RA / 32, B_INS = RB / 32;   // DMA instructions per wave and slab
+  static constexpr int A_BYTES = RA * 128, SLAB = A_BYTES + RB * BK * BE;
+  static constexpr int A_INS = RA / 32, B_INS = RB * BK * BE / 4096;   // DMA instructions per wave and slab
   static constexpr int INS = A_INS + B_INS;
   static constexpr int LDS = NS * SLAB;
   static_assert(WM * WN * WK == 4 && TM % 32 == 0 && TN % 32 == 0, "4 waves of 32-multiples");
@@ -139,6 +143,97 @@ template <typename T, bool KC, int R, bool INTER> struct TileDma {
   }
 };
 
+// The same for int8 codes, K-contiguous: slab rows of 64 bytes, the 16-byte chunk
+// index XOR-swizzled by (r >> 2) & 3 (as I8Frag reads them), an instruction 16
+// rows.  The pointers and ld of the operand count bytes.
+template <int R, bool INTER> struct TileDmaI8 {
+  static constexpr int BK = 64;
+  static constexpr int NI = R / 64;      // instructions per wave and slab
+  static constexpr int NB = INTER ? NI : 1;
+  uint32_t off[NI];
+  uintptr_t base[NB];
+  int ins0;
+
+  __device__ __forceinline__ static uint32_t lane_off(const TileSrc<int8_t>& s, int ins, int lane, int kv) {
+    const int r = 16 * ins + (lane >> 2);
+    const int k = 16 * ((lane & 3) ^ swz_kc(r));
+    const int pr = INTER ? 32 * (r >> 6) + (r & 31) : r;
+    return (uint32_t)((size_t)min(pr, s.rows - 1) * s.ld + min(k, kv - 16));   // kv is a multiple of 16
+  }
+  __device__ __forceinline__ void rebase(const TileSrc<int8_t>& s, bool) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      base[u] = (uintptr_t)s.p;
+      if (INTER) base[u] += ((ins0 + u) >> 1) & 1 ? (uintptr_t)s.p2 - (uintptr_t)s.p : 0;
+    }
+  }
+  __device__ __forceinline__ void init(const TileSrc<int8_t>& s) {
+    const int lane = lane_id();
+    ins0 = wave_id() * NI;
+#pragma unroll
+    for (int u = 0; u < NI; ++u) off[u] = lane_off(s, ins0 + u, lane, BK);
+    rebase(s, false);
+  }
+  __device__ __forceinline__ void issue(const TileSrc<int8_t>& s, int kv, FM_LDS char* tile) {
+    const int lane = lane_id_here();
+#pragma unroll
+    for (int u = 0; u < NI; ++u)
+      dma16s((const void*)base[INTER ? u : 0], kv >= BK ? off[u] : lane_off(s, ins0 + u, lane, kv),
+             tile + (ins0 + u) * 1024);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) base[u] += 64;
+  }
+  __device__ __forceinline__ static void zero_tail(int kv, FM_LDS char* tile) {
+    for (int c = threadIdx.x; c < R * 4; c += 256)
+      if (16 * ((c & 3) ^ swz_kc(c >> 2)) >= kv) *(FM_LDS u32x4_t*)(tile + 16 * c) = u32x4_t{0, 0, 0, 0};
+  }
+};
+
+// Eight int8 codes -> eight bf16 (exact: |q| <= 128 has at most 8 significant
+// bits).  One SDWA conversion per code straight from its byte, one byte permute
+// per pair of high halves: 12 instructions.  Written out because the compiler
+// turned the shifts of plain C++ into 28 (shift, sign-extending extract,
+// conversion, shift, and-or).
+template <int BYTE> __device__ __forceinline__ uint32_t cvt_code(uint32_t x) {
+  uint32_t f;
+  if constexpr (BYTE == 0)
+    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(f) : "v"(x));
+  else if constexpr (BYTE == 1)
+    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1" : "=v"(f) : "v"(x));
+  else if constexpr (BYTE == 2)
+    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(f) : "v"(x));
+  else
+    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3" : "=v"(f) : "v"(x));
+  return f;
+}
+__device__ __forceinline__ bf16x8_t widen_i8x8(u32x2_t raw) {
+  u32x4_t v;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    v[2 * i] = __builtin_amdgcn_perm(cvt_code<1>(raw[i]), cvt_code<0>(raw[i]), 0x07060302u);
+    v[2 * i + 1] = __builtin_amdgcn_perm(cvt_code<3>(raw[i]), cvt_code<2>(raw[i]), 0x07060302u);
+  }
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+
+// Fragments of an int8 slab: lane l holds row r0 + l % 32 and k 16 ks +
+// 8 (l / 32) + 0..7, i.e. 8 bytes of chunk ks (swizzled).
+// Sixteen consecutive rows read 16 distinct 2-bank groups.
+template <int R, int NB> struct I8Frag {
+  uint32_t off[NB];
+  __device__ __forceinline__ void init(int row0) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int r = row0 + i * 32 + (lane & 31);
+      off[i] = (uint32_t)(r * 64 + (swz_kc(r) << 4) + 8 * (lane >> 5));
+    }
+  }
+  __device__ __forceinline__ u32x2_t codes(const FM_LDS char* tile, int i, int ks) const {
+    return *(const FM_LDS u32x2_t*)(tile + (off[i] ^ (uint32_t)(ks << 4)));
+  }
+};
+
 template <typename T> struct tile_frag;
 template <> struct tile_frag<bf16> { typedef bf16x8_t type; };
 template <> struct tile_frag<float> { typedef f32x4_t type; };
@@ -212,14 +307,16 @@ template <int N, int INS> __device__ __forceinline__ void tile_wait(int after) {
 // LDS must be free on entry and is free on return (a barrier ends the call).
 // Slab kt has landed once at most the NS - 2 slabs issued after it are in
 // flight; the barrier at the top of slab kt says that every wave has read slab
-// kt - 1, whose buffer then takes slab kt + NS - 1.  A wave issues all of a
-// slab's fragment reads, then the DMA of the coming slab (its address work
+// kt - 1, whose buffer then takes slab kt + NS - 1.  A wave issues a slab's
+// fragment reads, then the DMA of the coming slab (its address work
 // covers the first reads' latency), then the MFMAs.  The partial last slab is
 // zero-filled in LDS, so that one copy of the MFMA code serves all slabs.
 template <class C, bool AKC, bool BKC, bool AI = false, bool BI = false, bool TWO = false>
-__device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const TileSrc<typename C::T>& B, int K,
+__device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const TileSrc<typename C::TB>& B, int K,
                                           FM_LDS char* lds, B16Acc<C::MI, C::NJ>& acc) {
   typedef typename C::T T;
+  constexpr bool I8 = C::BE == 1;
+  static_assert(!I8 || (BKC && !TWO), "int8 B is K-contiguous, one product");
   typedef typename tile_frag<T>::type frag;
   const int n1 = (K + C::BK - 1) / C::BK;
   const int nk = TWO ? 2 * n1 : n1;
@@ -229,14 +326,16 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
   }
   const int wave = wave_id();
   TileDma<T, AKC, C::RA, AI> da;
-  TileDma<T, BKC, C::RB, BI> db;
+  std::conditional_t<I8, TileDmaI8<C::RB, BI>, TileDma<T, BKC, C::RB, BI>> db;
   da.init(A);
   db.init(B);
   TileFrag<T, AKC, C::RA, C::MI> fa;
-  TileFrag<T, BKC, C::RB, C::NJ> fb;
+  std::conditional_t<I8, I8Frag<C::RB, C::NJ>, TileFrag<T, BKC, C::RB, C::NJ>> fb;
   fa.init((wave % C::WM) * C::TM);
   fb.init((wave / C::WM % C::WN) * C::TN);
   constexpr int KW = C::KS / C::WK;   // steps per wave and slab
+  // steps whose fragments are read ahead (all, where the registers allow)
+  constexpr int SB = C::MI * C::NJ >= 8 && KW > 2 ? 2 : KW;
   const int st0 = wave / (C::WM * C::WN) * KW;
   auto issue = [&](int s, int buf) {
     if (TWO && s == n1) {
@@ -264,23 +363,36 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
       db.zero_tail(kv, tb);
       tile_barrier();
     }
-    frag xa[KW][C::MI], xb[KW][C::NJ];
+    // int8 codes are widened next to their MFMAs
+    typedef std::conditional_t<I8, u32x2_t, frag> bfrag;
+    frag xa[SB][C::MI];
+    bfrag xb[SB][C::NJ];
+    auto read = [&](int st) {
 #pragma unroll
-    for (int st = 0; st < KW; ++st) {
+      for (int i = 0; i < C::MI; ++i) xa[st % SB][i] = fa.read(ta, i, st0 + st);
 #pragma unroll
-      for (int i = 0; i < C::MI; ++i) xa[st][i] = fa.read(ta, i, st0 + st);
+      for (int j = 0; j < C::NJ; ++j) {
+        if constexpr (I8) xb[st % SB][j] = fb.codes(tb, j, st0 + st);
+        else xb[st % SB][j] = fb.read(tb, j, st0 + st);
+      }
+    };
 #pragma unroll
-      for (int j = 0; j < C::NJ; ++j) xb[st][j] = fb.read(tb, j, st0 + st);
-    }
+    for (int st = 0; st < SB; ++st) read(st);
     sched_fence();
     if (kt + C::NS - 1 < nk) issue(kt + C::NS - 1, nxt);
     sched_fence();
 #pragma unroll
-    for (int st = 0; st < KW; ++st)
+    for (int st = 0; st < KW; ++st) {
 #pragma unroll
-      for (int i = 0; i < C::MI; ++i)
+      for (int j = 0; j < C::NJ; ++j) {
+        frag b;
+        if constexpr (I8) b = widen_i8x8(xb[st % SB][j]);
+        else b = xb[st % SB][j];
 #pragma unroll
-        for (int j = 0; j < C::NJ; ++j) acc.v[i][j] = tile_mma(xb[st][j], xa[st][i], acc.v[i][j]);
+        for (int i = 0; i < C::MI; ++i) acc.v[i][j] = tile_mma(b, xa[st % SB][i], acc.v[i][j]);
+      }
+      if (st + SB < KW) read(st + SB);
+    }
     cur = cur + 1 == C::NS ? 0 : cur + 1;
     nxt = nxt + 1 == C::NS ? 0 : nxt + 1;
   }

@@ -1,6 +1,6 @@
 """The grouped FFN at the sizes where its tile shapes change: each small tile
 (32, 64 and 128 rows), the large one, and both ways to pair them with the
-weight gradients' tiles, at row, column and k remainders (d and I multiples of
+weight gradients' tiles, and the int8 forward's, at row, column and k remainders (d and I multiples of
 8, a single token, empty tuning slots, shared experts).  A whole step through
 the C ABI against the fp64 oracle on the oracle's routing."""
 import numpy as np
@@ -11,6 +11,7 @@ import oracle as O
 from paper_2508_19078_amd import api, workloads as W
 from paper_2508_19078_amd.layer import LayerInputs, MoELayerRunner
 
+import test_gpu_quantized_forward as Q8
 from gpu_harness import TOL_FFN, OracleLayer, host, log, rel_fro
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +76,17 @@ def test_step(w):
     for i, got in enumerate(once):
         for a, t in zip(got, (r.dWg, r.dWu, r.dWd)):
             np.testing.assert_array_equal(host(t[i]), 2 * a)
+
+
+# (T, d, E, k, I, shared, experts drawn from, sampled rows) of the int8 forward's tiles
+Q8_CASES = {
+    "tiles_q8_32": (20, 80, 8, 2, 48, 1, 7, None),         # r = 7, an empty slot
+    "tiles_q8_64": (260, 144, 6, 2, 112, 0, 6, None),      # r = 87, 12 128-row tiles
+    "tiles_q8_128": (1600, 144, 64, 6, 336, 0, 63, None),  # r = 150, 320 128-row tiles; I and d end inside a slab
+}
+
+
+@pytest.mark.parametrize("name", list(Q8_CASES))
+def test_int8_forward(name, monkeypatch):
+    monkeypatch.setitem(Q8.CASES, name, Q8_CASES[name])
+    Q8.test_quantised_forward(name)
