@@ -1092,7 +1092,7 @@ extern "C" int moe_grouped_swiglu_bwd(const moe_layer* L, const void* X, const v
       tile_dh(plan, L, offsets, T, k, A_g, A_u, dO, dAg, dAu, ldA, bw.norms, st);
   }
   if (!big_dw) {
-    tile_dw(plan, L, X, X_perm, offsets, T, k, H, dO, dAg, dAu, ldA, accumulate_dw, st);
+    tile_dw(L, X, X_perm, offsets, T, k, H, dO, dAg, dAu, ldA, accumulate_dw, st);
   } else if (accumulate_dw) {
     hipLaunchKernelGGL(kb_dw_d<true>, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)dO, (cbp)H, da_d);
     hipLaunchKernelGGL(kb_dw_gu<true>, grid, block, 0, st, layer_ptrs<bf16>(L), (cbp)X, (cbp)X_perm, (cbp)dAg,

@@ -549,6 +549,7 @@ using F32 = TileCfg<float, 32, 64, 1, 2, 2, 4, 3>;
 using B32 = TileCfg<bf16, 32, 64, 1, 2, 2, 4, 3>;
 using B64 = TileCfg<bf16, 64, 128, 2, 2, 1, 3, 2>;
 using B128 = TileCfg<bf16, 128, 128, 2, 2, 1, 2, 2>;
+using D128 = TileCfg<bf16, 128, 128, 2, 2, 1, 4, 2, 2, 64>;   // weight gradients: half slabs, three in flight
 
 // int8 weights.  Widening a fragment costs 12 vector instructions, so a wave
 // covers all of the tile's rows (each code is widened once per wave, not once
@@ -557,7 +558,7 @@ using Q32 = TileCfg<bf16, 32, 128, 1, 2, 2, 4, 3, 1>;
 using Q64 = TileCfg<bf16, 64, 128, 1, 2, 2, 3, 3, 1>;
 using Q128 = TileCfg<bf16, 128, 256, 1, 4, 1, 2, 2, 1>;
 
-// Calls fn(C{}) with the tile of the plan's row products / weight gradients.
+// Calls fn(C{}) with the tile of the plan's row products.
 template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
   if (dtype == MOE_F32) {
     if (p.rows == TilePlan::ROWS_32) fn(F32{});
@@ -570,10 +571,17 @@ template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
     fn(B128{});
   }
 }
-template <class Fn> void with_dw(const TilePlan& p, int dtype, Fn fn) {
+// Weight gradients, each product by its 128 x 128 tiles (every slot counted as
+// tuning): 64 x 128 tiles with whole slabs where those would be fewer than five
+// per compute unit.  us on 64 x 128, 128 x 128: I = 512, d = 768, 32 slots, r =
+// 512: dW_down (768 tiles) 50, 59, dW_gate/up (1536) 80, 77; r = 128 22, 24 and
+// 40, 34; I = 256, d = 512, 16 slots, r = 2048 (128, 256 tiles) 66, 112 and 79,
+// 123; I = 376, d = 712, 32 slots, r = 375 (576, 1152) 35, 40 and 52, 55; I =
+// 1408, d = 2048, 64 slots, r = 96 114, 99 and 250, 187.
+template <class Fn> void with_dw(int dtype, long long tiles128, Fn fn) {
   if (dtype == MOE_F32) fn(F64{});
-  else if (p.dw == TilePlan::DW_64) fn(B64{});
-  else fn(B128{});
+  else if (tiles128 < 1280) fn(B64{});
+  else fn(D128{});
 }
 
 RowArgs row_args(const moe_layer* L, const int32_t* offsets, int T, int k, int ldA) {
@@ -608,7 +616,7 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   if (L->dtype == MOE_F32) {
     // r = 7.5 (60 tokens, d = 712, I = 376, 32 slots): fwd 36 against 51 us
     p.rows = few ? TilePlan::ROWS_32 : TilePlan::ROWS_64;
-    p.dw = TilePlan::DW_64;
+    p.dw = TilePlan::SMALL_DW;
     return p;
   }
   // Row products, the sum of gate-up, down, dH and dX in us on 64 x 128, 128 x
@@ -625,16 +633,15 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   else if (r <= 88 || (r <= 176 && mt128 * nt_gu <= 288)) p.rows = TilePlan::ROWS_64;
   else if (r <= 176 || (r <= 288 && mt256 * nt_gu256 < 512)) p.rows = TilePlan::ROWS_128;
   else p.rows = TilePlan::LARGE_ROWS;
-  // Weight gradients (dW_down + dW_gate/up in us: 64 x 128, 128 x 128, large;
-  // every slot counted as tuning): their tiles number with the weights, not with
-  // the rows.  I = 256, d = 512, 16 slots: r = 512 48, 76, 108; r = 2048 146, 255,
-  // 322.  I = 512, d = 768, 32 slots: r = 512 134, 156, 170.  I = 1408, d = 2048,
-  // 64 slots: r = 72 347, 277, 293; r = 192 460, 370, 378; r = 288 -, 422, 415.  I =
-  // 688, d = 4096, 16 slots: r = 128 197, 177, 169; r = 512 411, 310, 295; r =
-  // 1024 -, 509, 428.
-  const double dw128 = (double)S * ((L->I + 63) / 64) * ((L->d + 127) / 128);
+  // Weight gradients, dW_down + dW_gate/up in us on the tiles of with_dw and on
+  // the large ones: they need slots of about 288 rows and four tiles per compute
+  // unit (every slot counted as tuning) to gain from the large tiles.  I = 1408,
+  // d = 2048, 64 slots: r = 48 144, 157; r = 144 317, 343; r = 288 413, 423; r =
+  // 768 1625, 1181.  I = 688, d = 4096, 16 slots: r = 128 168, 171; r = 256 203, 214;
+  // r = 1024 487, 424.  I = 512, d = 768, 32 slots (384 large tiles): r = 512 127,
+  // 173; r = 1024 198, 264.  I = 256, d = 512, 16 slots: r = 2048 145, 323.
   const double dw256 = (double)S * ((L->I + 127) / 128) * ((L->d + 255) / 256);
-  p.dw = r > 176 && dw256 >= 1024 ? TilePlan::LARGE_DW : dw128 >= 2048 ? TilePlan::DW_128 : TilePlan::DW_64;
+  p.dw = r > 288 && dw256 >= 1024 ? TilePlan::LARGE_DW : TilePlan::SMALL_DW;
   return p;
 }
 
@@ -680,15 +687,19 @@ void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int 
   });
 }
 
-void tile_dw(const TilePlan& p, const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int Tn,
-             int k, const void* H, const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate,
-             hipStream_t st) {
+void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int Tn, int k, const void* H,
+             const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate, hipStream_t st) {
   const RowArgs ra = row_args(L, offsets, Tn, k, ldA);
-  with_dw(p, L->dtype, [&](auto c) {
+  const long long nd = cdiv(ra.d, 128);
+  with_dw(L->dtype, ra.S * nd * cdiv(ra.I, 128), [&](auto c) {
     typedef decltype(c) C;
     typedef typename C::T T;
     hipLaunchKernelGGL(kt_dw_d<C>, tile_grid<C>((long long)ra.S * cdiv(ra.d, C::RA) * cdiv(ra.I, C::RB)), dim3(256), 0,
                        st, layer_ptrs<T>(L), (const T*)dO, (const T*)H, ra, accumulate);
+  });
+  with_dw(L->dtype, ra.S * nd * cdiv(ra.I, 64), [&](auto c) {
+    typedef decltype(c) C;
+    typedef typename C::T T;
     hipLaunchKernelGGL(kt_dw_gu<C>, tile_grid<C>((long long)ra.S * cdiv(ra.I, C::RA / 2) * cdiv(ra.d, C::RB)),
                        dim3(256), 0, st, layer_ptrs<T>(L), (const T*)X, (const T*)Xp, (const T*)dAg, (const T*)dAu, ra,
                        accumulate);

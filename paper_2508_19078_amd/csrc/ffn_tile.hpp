@@ -10,7 +10,7 @@ namespace fm {
 // layer's shape, T and k (the bucket sizes are only known on the device).
 struct TilePlan {
   enum Rows { LARGE_ROWS, ROWS_32, ROWS_64, ROWS_128 } rows;   // gate-up, down, dH, dX
-  enum Dw { LARGE_DW, DW_64, DW_128 } dw;                      // dW_gate/up, dW_down
+  enum Dw { LARGE_DW, SMALL_DW } dw;                           // dW_gate/up, dW_down
 };
 TilePlan tile_plan(const moe_layer* L, int T, int k);
 // Columns of I per partial of the utility's row norms (the dH column tile).
@@ -21,8 +21,8 @@ void tile_fwd(const TilePlan& p, const moe_layer* L, const void* X, const void* 
 // dAg, dAu: [rows, ldA] scratch; norms: per row and dH column tile (sum dA^2, sum h^2).
 void tile_dh(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int T, int k, const void* Ag,
              const void* Au, const void* dO, void* dAg, void* dAu, int ldA, float2* norms, hipStream_t st);
-void tile_dw(const TilePlan& p, const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int T, int k,
-             const void* H, const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate, hipStream_t st);
+void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int T, int k, const void* H,
+             const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate, hipStream_t st);
 void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int T, int k, const void* dAg,
              const void* dAu, int ldA, void* dXp, hipStream_t st);
 

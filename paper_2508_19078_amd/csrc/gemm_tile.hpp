@@ -36,23 +36,26 @@ namespace fm {
 // ring, BPC blocks per compute unit (what the ring leaves room for).
 // BE: bytes per B element, sizeof(T) or 1 (int8 codes widened exactly to bf16 as
 // fragments are read; K-contiguous, 64-byte slab rows).
-template <typename T_, int RA_, int RB_, int WM_, int WN_, int WK_, int NS_, int BPC_, int BE_ = (int)sizeof(T_)>
+// KR: bytes of k per slab row, 128 or 64.
+template <typename T_, int RA_, int RB_, int WM_, int WN_, int WK_, int NS_, int BPC_, int BE_ = (int)sizeof(T_),
+          int KR_ = 128>
 struct TileCfg {
   typedef T_ T;
   typedef std::conditional_t<BE_ == 1, int8_t, T_> TB;
-  static constexpr int RA = RA_, RB = RB_, WM = WM_, WN = WN_, WK = WK_, NS = NS_, BPC = BPC_, BE = BE_;
+  static constexpr int RA = RA_, RB = RB_, WM = WM_, WN = WN_, WK = WK_, NS = NS_, BPC = BPC_, BE = BE_, KR = KR_;
   static constexpr int THREADS = 256;
   static constexpr int V = 16 / (int)sizeof(T);       // elements per 16 bytes
-  static constexpr int BK = 8 * V;                    // k per slab (128 bytes)
-  static constexpr int KS = 4;                        // MFMA steps per slab
+  static constexpr int BK = KR / (int)sizeof(T);      // k per slab
+  static constexpr int KS = KR / 32;                  // MFMA steps per slab
   static constexpr int TM = RA / WM, TN = RB / WN;    // wave sub-tile
   static constexpr int MI = TM / 32, NJ = TN / 32;    // MFMA tiles per wave
-  static constexpr int A_BYTES = RA * 128, SLAB = A_BYTES + RB * BK * BE;
-  static constexpr int A_INS = RA / 32, B_INS = RB * BK * BE / 4096;   // DMA instructions per wave and slab
+  static constexpr int A_BYTES = RA * KR, SLAB = A_BYTES + RB * BK * BE;
+  static constexpr int A_INS = A_BYTES / 4096, B_INS = RB * BK * BE / 4096;   // DMA instructions per wave and slab
   static constexpr int INS = A_INS + B_INS;
   static constexpr int LDS = NS * SLAB;
   static_assert(WM * WN * WK == 4 && TM % 32 == 0 && TN % 32 == 0, "4 waves of 32-multiples");
   static_assert(NS >= 2 && BPC * (LDS + 6 * 1024) <= 160 * 1024 + 5 * 1024 && (NS - 2) * INS < 64, "ring");
+  static_assert(KR == 128 || (KR == 64 && sizeof(T) == 2 && BE == 2), "slab rows");
   static_assert(WK == 1 || (WK - 1) * RA * RB * 4 <= LDS, "partial sums");
 };
 
@@ -67,9 +70,11 @@ template <typename T> struct TileSrc {
   int rows;
 };
 
-template <typename T, bool KC, int R, bool INTER> struct TileDma {
-  static constexpr int V = 16 / (int)sizeof(T), BK = 8 * V;
-  static constexpr int NI = R / 32;      // instructions per wave and slab
+template <typename T, bool KC, int R, bool INTER, int KR> struct TileDma {
+  static constexpr int V = 16 / (int)sizeof(T), BK = KR / (int)sizeof(T);
+  static constexpr int NI = R * KR / 4096;   // instructions per wave and slab
+  static constexpr int RPI = 1024 / KR;      // rows per instruction (KC)
+  static constexpr int CPR = KR / 16;        // chunks per row (KC)
   static constexpr int CB = R / 32;      // column blocks (MN)
   static constexpr int NB = INTER ? NI : 1;
   uint32_t off[NI];
@@ -77,16 +82,18 @@ template <typename T, bool KC, int R, bool INTER> struct TileDma {
   uintptr_t step;
   int ins0;             // this wave's first instruction
 
-  __device__ __forceinline__ static int block_of(int ins) { return KC ? ins >> 2 : ins % CB; }   // 32-row block
+  __device__ __forceinline__ static int block_of(int ins) { return KC ? ins * RPI / 32 : ins % CB; }   // 32-row block
   __device__ __forceinline__ static int lds_at(int ins) {
-    return KC ? ins * 1024 : (ins % CB) * 4096 + (ins / CB) * 1024;
+    return KC ? ins * 1024 : (ins % CB) * (32 * KR) + (ins / CB) * 1024;
   }
+  // Chunk swizzle of a K-contiguous row.
+  __device__ __forceinline__ static int swz(int r) { return KR == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
   // Byte offset (from the matrix of the instruction's block at the slab's first
   // k) of this lane's 16 bytes; kv = valid k from there on.
   __device__ __forceinline__ static uint32_t lane_off(const TileSrc<T>& s, int ins, int lane, int kv) {
     if (KC) {
-      const int r = 8 * ins + (lane >> 3);
-      const int k = V * ((lane & 7) ^ ((r >> 1) & 7));
+      const int r = RPI * ins + lane / CPR;
+      const int k = V * (lane % CPR ^ swz(r));
       const int pr = INTER ? 32 * (r >> 6) + (r & 31) : r;
       return (uint32_t)(((size_t)min(pr, s.rows - 1) * s.ld + min(k, kv - V)) * sizeof(T));
     }
@@ -112,7 +119,7 @@ template <typename T, bool KC, int R, bool INTER> struct TileDma {
   __device__ __forceinline__ void init(const TileSrc<T>& s) {
     const int lane = lane_id();
     ins0 = wave_id() * NI;
-    step = KC ? 128 : (uintptr_t)BK * s.ld * sizeof(T);
+    step = KC ? KR : (uintptr_t)BK * s.ld * sizeof(T);
 #pragma unroll
     for (int u = 0; u < NI; ++u) off[u] = lane_off(s, ins0 + u, lane, BK);
     rebase(s, false);
@@ -133,10 +140,10 @@ template <typename T, bool KC, int R, bool INTER> struct TileDma {
   }
   // Zeroes the slab's k >= kv in LDS (the block's 256 threads; after the slab has landed).
   __device__ __forceinline__ static void zero_tail(int kv, FM_LDS char* tile) {
-    for (int c = threadIdx.x; c < R * 8; c += 256) {   // 16-byte chunks
+    for (int c = threadIdx.x; c < R * CPR; c += 256) {   // 16-byte chunks
       int k;
-      if (KC) k = V * ((c & 7) ^ ((c >> 4) & 7));      // row c / 8
-      else if (sizeof(T) == 2) k = (c >> 2) & 63;      // 64-byte k-rows
+      if (KC) k = V * (c % CPR ^ swz(c / CPR));
+      else if (sizeof(T) == 2) k = (c >> 2) % BK;      // 64-byte k-rows
       else k = 8 * ((c >> 6) & 3) + ((c >> 4) & 3) + 4 * ((c >> 3) & 1);   // 128-byte k-rows, permuted in groups of 8
       if (k >= kv) *(FM_LDS u32x4_t*)(tile + 16 * c) = u32x4_t{0, 0, 0, 0};
     }
@@ -240,7 +247,7 @@ template <> struct tile_frag<float> { typedef f32x4_t type; };
 
 // MFMA fragments: lane l holds row r0 + l % 32 and k KST * step +
 // (KST / 2) (l / 32) + 0 .. KST / 2 - 1 (16 bytes) of each 32-row block.
-template <typename T, bool KC, int R, int NB> struct TileFrag {
+template <typename T, bool KC, int R, int NB, int KR> struct TileFrag {
   typedef typename tile_frag<T>::type frag;
   uint32_t off[NB];
 
@@ -251,12 +258,12 @@ template <typename T, bool KC, int R, int NB> struct TileFrag {
       const int r0 = row0 + 32 * i;
       if (KC) {
         const int r = r0 + (lane & 31);
-        off[i] = (uint32_t)(r * 128 + (((lane >> 5) ^ ((r >> 1) & 7)) << 4));
+        off[i] = (uint32_t)(r * KR + (((lane >> 5) ^ TileDma<T, KC, R, false, KR>::swz(r)) << 4));
       } else if (sizeof(T) == 2) {
         // as B16Frag: output lane i, element j of a 16-lane group comes from
         // the address of lane 4 j + i / 4, offset i % 4
         const int g = lane >> 4, L = lane & 15;
-        off[i] = (uint32_t)((r0 >> 5) * 4096 + (8 * (g >> 1) + (L >> 2)) * 64 + (16 * (g & 1) + 4 * (L & 3)) * 2);
+        off[i] = (uint32_t)((r0 >> 5) * (32 * KR) + (8 * (g >> 1) + (L >> 2)) * 64 + (16 * (g & 1) + 4 * (L & 3)) * 2);
       } else {
         off[i] = (uint32_t)((r0 >> 5) * 4096 + (lane >> 5) * 128 + (lane & 31) * 4);
       }
@@ -325,12 +332,12 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
     return;
   }
   const int wave = wave_id();
-  TileDma<T, AKC, C::RA, AI> da;
-  std::conditional_t<I8, TileDmaI8<C::RB, BI>, TileDma<T, BKC, C::RB, BI>> db;
+  TileDma<T, AKC, C::RA, AI, C::KR> da;
+  std::conditional_t<I8, TileDmaI8<C::RB, BI>, TileDma<T, BKC, C::RB, BI, C::KR>> db;
   da.init(A);
   db.init(B);
-  TileFrag<T, AKC, C::RA, C::MI> fa;
-  std::conditional_t<I8, I8Frag<C::RB, C::NJ>, TileFrag<T, BKC, C::RB, C::NJ>> fb;
+  TileFrag<T, AKC, C::RA, C::MI, C::KR> fa;
+  std::conditional_t<I8, I8Frag<C::RB, C::NJ>, TileFrag<T, BKC, C::RB, C::NJ, C::KR>> fb;
   fa.init((wave % C::WM) * C::TM);
   fb.init((wave / C::WM % C::WN) * C::TN);
   constexpr int KW = C::KS / C::WK;   // steps per wave and slab

@@ -33,7 +33,8 @@ CASES = [
     _w(130, 264, 8, 4, 136),                   # r = 65: 64-row tile
     _w(150, 136, 4, 2, 24, ns=1),              # r = 90 but few tiles: 64-row tile
     _w(800, 1032, 64, 8, 264),                 # r = 100: 128-row tile, 128-row dW tile
-    _w(1600, 520, 64, 8, 776, bias="zipf"),    # r = 200: large dW tile
+    _w(1600, 520, 64, 8, 776, bias="zipf"),    # r = 200, large d, 128-row dW tiles
+    _w(2400, 520, 64, 8, 776),                 # r = 300: large tiles throughout
     _w(700, 136, 4, 2, 72),                    # r = 350: large tile, 64-row dW tile
     _w(2, 40, 4, 1, 24, "f32"),                # fp32, empty slots, k below one slab
     _w(40, 136, 8, 4, 72, "f32", ns=1),        # r = 22: 32-row tile
