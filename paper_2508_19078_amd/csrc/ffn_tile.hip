@@ -106,8 +106,8 @@ template <> __device__ __forceinline__ float tile_sigm<bf16>(float z) { return s
 
 template <class C> __device__ __forceinline__ AccCoord tile_coord(int i, int j, int q) {
   const int lane = lane_id(), wave = wave_id();
-  return AccCoord{(wave % C::WM) * C::TM + i * 32 + (lane & 31),
-                  (wave / C::WM % C::WN) * C::TN + j * 32 + 8 * q + 4 * (lane >> 5)};
+  return AccCoord{tile_row0<C>(wave) + i * 32 + (lane & 31),
+                  tile_col0<C>(wave) + j * 32 + 8 * q + 4 * (lane >> 5)};
 }
 
 // Whether this wave holds accumulators after tile_gemm (the waves with wk = 0).
