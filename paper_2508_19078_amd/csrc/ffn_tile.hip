@@ -360,6 +360,15 @@ __device__ __forceinline__ int tile_dw_order(FM_LDS int* key, short* order, cons
   return n;
 }
 
+// Zeros part i of n of a weight gradient of `count` floats, as one contiguous run
+// (the gradient of a slot without rows; one that accumulates has nothing to add
+// and is skipped).  Written tile by tile, rows that are not whole 128-byte lines
+// were stored at half the rate.
+__device__ __forceinline__ void zero_part(float* p, long long count, int i, int n) {
+  const long long c4 = count / 4, hi = c4 * (i + 1) / n;
+  for (long long c = c4 * i / n + threadIdx.x; c < hi; c += 256) st16(p + 4 * c, u32x4_t{0, 0, 0, 0});
+}
+
 // dW_gate = dA_g^T X_s and dW_up = dA_u^T X_s in one product: the A tile
 // interleaves 32-column blocks of dA_g and dA_u (RA / 2 intermediate rows of
 // both per tile); both operands read k-major, k = the slot's rows.
@@ -387,19 +396,24 @@ __global__ __launch_bounds__(256, C::BPC) void kt_dw_gu(LayerPtrs<typename C::T>
     band_order(t % tps, MT, NT, 8, m, n);
     const SlotRows sr = slot_rows(s, ra.offsets, ra.S_r, ra.Tn, ra.k);
     const int m0 = m * CI, n0 = n * C::RB;
+    auto row_ptr = [=](int r) {
+      const int mm = m0 + 32 * (r >> 6) + (r & 31);
+      return mm < I ? ((r >> 5) & 1 ? dwu : dwg) + (size_t)mm * d + n0 : (float*)nullptr;
+    };
+    if (sr.nrows == 0) {
+      if (!accumulate) {
+        zero_part(dwg, (long long)I * d, t % tps, tps);
+        zero_part(dwu, (long long)I * d, t % tps, tps);
+      }
+      continue;
+    }
     const TileSrc<T> A{dAg + (size_t)sr.orow0 * ld + m0, dAu + (size_t)sr.orow0 * ld + m0, nullptr, ld, I - m0};
     const TileSrc<T> B{(sr.shared ? X : Xp) + (size_t)sr.xrow0 * d + n0, nullptr, nullptr, d, d - n0};
     B16Acc<C::MI, C::NJ> acc;
     acc.zero();
     tile_gemm<C, false, false, true, false>(A, B, sr.nrows, lds, acc);
     tile_stage<C, float>(acc, lds);
-    Stage<float, C::RB>::template copy_rows<C::RA, 256>(
-        lds,
-        [=](int r) {
-          const int mm = m0 + 32 * (r >> 6) + (r & 31);
-          return mm < I ? ((r >> 5) & 1 ? dwu : dwg) + (size_t)mm * d + n0 : (float*)nullptr;
-        },
-        d - n0, accumulate);
+    Stage<float, C::RB>::template copy_rows<C::RA, 256>(lds, row_ptr, d - n0, accumulate);
     barrier_lds();
   }
 }
@@ -425,14 +439,18 @@ __global__ __launch_bounds__(256, C::BPC) void kt_dw_d(LayerPtrs<typename C::T> 
     band_order(t % tps, MT, NT, 8, m, n);
     const SlotRows sr = slot_rows(s, ra.offsets, ra.S_r, ra.Tn, ra.k);
     const int m0 = m * C::RA, n0 = n * C::RB;
+    auto row_ptr = [=](int r) { return m0 + r < d ? dwd + (size_t)(m0 + r) * I + n0 : (float*)nullptr; };
+    if (sr.nrows == 0) {
+      if (!accumulate) zero_part(dwd, (long long)I * d, t % tps, tps);
+      continue;
+    }
     const TileSrc<T> A{dO + (size_t)sr.orow0 * d + m0, nullptr, nullptr, d, d - m0};
     const TileSrc<T> B{H + (size_t)sr.orow0 * I + n0, nullptr, nullptr, I, I - n0};
     B16Acc<C::MI, C::NJ> acc;
     acc.zero();
     tile_gemm<C, false, false>(A, B, sr.nrows, lds, acc);
     tile_stage<C, float>(acc, lds);
-    Stage<float, C::RB>::template copy_rows<C::RA, 256>(
-        lds, [=](int r) { return m0 + r < d ? dwd + (size_t)(m0 + r) * I + n0 : (float*)nullptr; }, I - n0, accumulate);
+    Stage<float, C::RB>::template copy_rows<C::RA, 256>(lds, row_ptr, I - n0, accumulate);
     barrier_lds();
   }
 }
