@@ -1,8 +1,8 @@
 // Gate re-routing and token permutation into per-slot buckets, the combine,
 // and their backward passes.
 //
-// Permute runs in two launches (three when slots x count blocks exceed 16384),
-// all deterministic:
+// Permute runs in one launch for up to PM_ONE choices, else in two (three when
+// slots x count blocks exceed 16384), all deterministic:
 //   count          a block of 256 tokens counts its rows per slot (LDS integer
 //                  atomics)
 //   [scan]         for large tables, one block turns the per-block counts into
@@ -11,7 +11,8 @@
 //   place+scatter  a block of 16 or 32 tokens ranks its rows within each slot in
 //                  token order, writes the maps and copies X[t] to every row t
 //                  opens (16-byte accesses, the row loads issued first); for
-//                  small tables it sums the count table itself
+//                  small tables it sums the count table itself, and for few
+//                  tokens it counts them all itself (no count launch)
 // Combine and the two backward gathers run one wave per token.
 #include <stdlib.h>
 
@@ -27,6 +28,12 @@ namespace {
 constexpr int PM_TOK = 256;   // tokens (threads) per block of count/place
 constexpr int PM_SMAX = 512;  // slots count and place support
 constexpr int PM_FUSE = 16384;  // place sums the count table itself up to this many entries
+// Choices (T k) up to which every place block counts all tokens itself instead
+// of reading a count launch's table.  us with and without that launch: T k = 32
+// 9.2, 8.1; 512 6.0, 4.5; 1998 12.2, 10.8; 3108 14.5, 14.2; 4096 6.9, 6.2; 6144
+// 14.0, 14.2; 8192 13.3, 15.8.
+constexpr int PM_ONE = 4096;
+enum { PLACE_POS = 0, PLACE_SCAN = 1, PLACE_ALL = 2 };   // what place gets: row positions, counts, nothing
 constexpr int PS_THREADS = 512;  // place + scatter: 8 waves of 16 or 32 tokens per block
 
 template <int KMAX>
@@ -128,9 +135,10 @@ __global__ __launch_bounds__(1024) void k_perm_scan(int32_t* __restrict__ bc, in
 //   2. the rows the count block's earlier tokens open are counted per slot (LDS
 //      integer atomics); this block's own tokens OR their bit into one 64-bit
 //      mask per slot, so a row's rank among them is a popcount (order-free);
-//      with SCAN the block also folds the count table into the slot totals and
-//      the rows of the count blocks before its own (and block 0 writes the
-//      bucket offsets), otherwise bc already holds those positions;
+//      with PLACE_SCAN the block also folds the count table into the slot totals
+//      and the rows of the count blocks before its own (and block 0 writes the
+//      bucket offsets), with PLACE_ALL it counts every token's rows itself,
+//      otherwise bc already holds those positions;
 //   3. the maps are written and each row is stored at every position its token
 //      opens.
 // s + the squares of the 16 bytes' elements (bf16, or fp32 when f32), in order.
@@ -149,18 +157,19 @@ __device__ __forceinline__ float sq_acc(const u32x4_t& v, bool f32, float s) {
   return s;
 }
 
-template <int KMAX, bool SCAN, int PS_TOK>
+template <int KMAX, int MODE, int PS_TOK>
 __global__ __launch_bounds__(PS_THREADS) void k_place_scatter(
     const int32_t* __restrict__ idx, const float* __restrict__ gate, const int32_t* __restrict__ emap,
     int T, int k, int S, const int32_t* __restrict__ bc, int nblk, int32_t* __restrict__ offsets,
     int32_t* __restrict__ perm_token, float* __restrict__ perm_gate, int32_t* __restrict__ inv,
     const char* __restrict__ X, int row_bytes, char* __restrict__ Xp, bool xf32, float* __restrict__ x_sq) {
+  constexpr bool SCAN = MODE == PLACE_SCAN, ALL = MODE == PLACE_ALL;
   constexpr int NTW = PS_TOK / (PS_THREADS / 64);   // tokens per wave
   constexpr int U = 4;                              // 16-byte chunks per lane and row per pass
   __shared__ unsigned long long msk[PM_SMAX];       // this block's tokens, one bit each, per slot
   __shared__ int pre[PM_SMAX];                      // rows of the count block's earlier tokens
   __shared__ int base[PM_SMAX];                     // this block's first row in each slot
-  __shared__ int tot[SCAN ? PM_SMAX : 1];           // rows of each slot over all tokens
+  __shared__ int tot[MODE != PLACE_POS ? PM_SMAX : 1];   // rows of each slot over all tokens
   __shared__ int posl[PS_TOK][KMAX];                // row of each choice that opens one, else -1
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const int t0 = blockIdx.x * PS_TOK;
@@ -177,9 +186,9 @@ __global__ __launch_bounds__(PS_THREADS) void k_place_scatter(
       if (t < T && c < row_bytes) v[x][u] = ld16(src + c);
     }
   }
-  const int tg = grp * PM_TOK + tid;
-  const bool mine = tid < PM_TOK && tg >= t0 && tg < t0 + PS_TOK && tg < T;
-  const bool earlier = tid < PM_TOK && tg < t0;
+  const int tg = ALL ? t0 + tid : grp * PM_TOK + tid;
+  const bool mine = ALL ? tid < PS_TOK && tg < T : tid < PM_TOK && tg >= t0 && tg < t0 + PS_TOK && tg < T;
+  const bool earlier = !ALL && tid < PM_TOK && tg < t0;
   TokenSlots<KMAX> ts;
   if (mine || earlier) {
     token_slots<KMAX>(idx, emap, tg, k, ts);
@@ -200,8 +209,8 @@ __global__ __launch_bounds__(PS_THREADS) void k_place_scatter(
   for (int s = tid; s < S; s += PS_THREADS) {
     msk[s] = 0ull;
     pre[s] = 0;
-    if (SCAN) tot[s] = 0;
-    base[s] = SCAN ? 0 : bc[(size_t)s * nblk + grp];
+    if (MODE != PLACE_POS) tot[s] = 0;
+    base[s] = MODE != PLACE_POS ? 0 : bc[(size_t)s * nblk + grp];
   }
   __syncthreads();
   // 2. counts and masks
@@ -211,6 +220,18 @@ __global__ __launch_bounds__(PS_THREADS) void k_place_scatter(
     if (!ts.first[j]) continue;
     if (earlier) atomicAdd(&pre[ts.s[j]], 1);
     else atomicOr(&msk[ts.s[j]], 1ull << me);
+  }
+  if (ALL) {
+    for (int t = tid; t < T; t += PS_THREADS) {
+      TokenSlots<KMAX> o;
+      token_slots<KMAX>(idx, emap, t, k, o);
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) {
+        if (!o.first[j]) continue;
+        atomicAdd(&tot[o.s[j]], 1);
+        if (t < t0) atomicAdd(&pre[o.s[j]], 1);
+      }
+    }
   }
   for (int i0 = 0; i0 < n; i0 += 4 * PS_THREADS) {
     if (i0 > 0) {
@@ -231,7 +252,7 @@ __global__ __launch_bounds__(PS_THREADS) void k_place_scatter(
     }
   }
   __syncthreads();
-  if (SCAN) {
+  if (MODE != PLACE_POS) {
     if (wave == 0) {
       // exclusive scan of the slot totals: lane l takes a run of consecutive slots
       const int per = (S + 63) / 64, s0 = min(S, lane * per), s1 = min(S, s0 + per);
@@ -642,13 +663,14 @@ int permute_launch(const void* X, int dtype, const int32_t* idx, const float* ga
   }
   if (allow_debug && debug_checks()) FM_TRY(debug_check_routing(idx, expert_map, T, E, k, S_routed, st));
   const int nblk = cdiv(T, PM_TOK);
+  const bool one = (long long)T * k <= PM_ONE;
+  const bool fuse = (long long)nblk * S_routed <= PM_FUSE;
 #define FM_PC(KM) \
   hipLaunchKernelGGL(k_perm_count<KM>, dim3(nblk), dim3(PM_TOK), 0, st, idx, expert_map, T, k, S_routed, bc, \
                      nblk)
-  FM_KSWITCH(k, FM_PC)
+  if (!one) { FM_KSWITCH(k, FM_PC) }
 #undef FM_PC
-  const bool fuse = (long long)nblk * S_routed <= PM_FUSE;
-  if (!fuse) hipLaunchKernelGGL(k_perm_scan, dim3(1), dim3(1024), 0, st, bc, nblk, S_routed, offsets);
+  if (!one && !fuse) hipLaunchKernelGGL(k_perm_scan, dim3(1), dim3(1024), 0, st, bc, nblk, S_routed, offsets);
   const int row_bytes = d * esize(dtype);
   // 32-token blocks once they fill every compute unit, else 16-token ones
   const bool wide = cdiv(T, 32) >= cu_count();
@@ -656,11 +678,12 @@ int permute_launch(const void* X, int dtype, const int32_t* idx, const float* ga
   hipLaunchKernelGGL((k_place_scatter<KM, SC, TOK>), dim3(cdiv(T, TOK)), dim3(PS_THREADS), 0, st, idx, gate, \
                      expert_map, T, k, S_routed, bc, nblk, offsets, perm_token, perm_gate, inv,             \
                      (const char*)X, row_bytes, (char*)X_perm, dtype == MOE_F32, x_sq)
-#define FM_PP(KM)                       \
-  if (fuse && wide) FM_PS(KM, true, 32);  \
-  else if (fuse) FM_PS(KM, true, 16);     \
-  else if (wide) FM_PS(KM, false, 32);    \
-  else FM_PS(KM, false, 16)
+#define FM_PP(KM)                             \
+  if (one) FM_PS(KM, PLACE_ALL, 16);            \
+  else if (fuse && wide) FM_PS(KM, PLACE_SCAN, 32); \
+  else if (fuse) FM_PS(KM, PLACE_SCAN, 16);     \
+  else if (wide) FM_PS(KM, PLACE_POS, 32);      \
+  else FM_PS(KM, PLACE_POS, 16)
   FM_KSWITCH(k, FM_PP)
 #undef FM_PP
 #undef FM_PS
