@@ -113,14 +113,14 @@ def exported_names() -> List[str]:
 
 # ------------------------------------------------------------- marshalling --
 
+_DTYPE_CODES = {torch.bfloat16: MOE_BF16, torch.float32: MOE_F32, torch.int8: MOE_I8}
+
+
 def dtype_code(t: torch.dtype) -> int:
-    if t == torch.bfloat16:
-        return MOE_BF16
-    if t == torch.float32:
-        return MOE_F32
-    if t == torch.int8:
-        return MOE_I8
-    raise TypeError(f"unsupported dtype {t}")
+    code = _DTYPE_CODES.get(t)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t}")
+    return code
 
 
 I32, F32, I64, U8, I8 = torch.int32, torch.float32, torch.int64, torch.uint8, torch.int8
@@ -136,16 +136,19 @@ def ptr(x, dt=None) -> Optional[int]:
     strided view would otherwise be misread silently."""
     if x is None:
         return None
-    if isinstance(x, int):
-        return x
     if isinstance(x, torch.Tensor):
+        # one pass over the three conditions: a call marshals a dozen tensors,
+        # and small layers are bound by this code
+        if x.is_cuda and x.is_contiguous() and (dt is None or x.dtype is dt or
+                                                (type(dt) is tuple and x.dtype in dt)):
+            return x.data_ptr()
         if not x.is_contiguous():
             raise ValueError(f"tensor argument of shape {tuple(x.shape)} is not contiguous")
         if x.device.type != "cuda":
             raise ValueError(f"tensor argument is on {x.device}, the library reads device memory")
-        if dt is not None and x.dtype not in (dt if isinstance(dt, tuple) else (dt,)):
-            raise TypeError(f"tensor argument has dtype {x.dtype}, expected {dt}")
-        return x.data_ptr()
+        raise TypeError(f"tensor argument has dtype {x.dtype}, expected {dt}")
+    if isinstance(x, int):
+        return x
     if isinstance(x, ctypes.Structure):
         return ctypes.addressof(x)
     if hasattr(x, "struct"):
@@ -155,14 +158,17 @@ def ptr(x, dt=None) -> Optional[int]:
 
 def stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        # the current device's current stream, without building a Stream object
+        if not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
 def _call(name: str, *args) -> int:
-    rc = getattr(lib(), name)(*args)
+    rc = getattr(_lib or lib(), name)(*args)
     if rc != MOE_OK:
         raise MoeError(rc, name, lib().moe_last_error().decode())
     return rc

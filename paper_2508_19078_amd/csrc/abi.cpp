@@ -2,6 +2,8 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <atomic>
+
 #include "common.hpp"
 
 namespace fm {
@@ -32,6 +34,17 @@ int need_dtype_float(int dtype, const char* name) {
   if (dtype != MOE_F32 && dtype != MOE_BF16)
     return fail(MOE_ERR_UNSUPPORTED, "%s=%d: expected MOE_F32 or MOE_BF16", name, dtype);
   return MOE_OK;
+}
+
+int device_cus() {
+  static std::atomic<int> known[64];   // by device, 0 = not asked yet
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  const bool slot = dev >= 0 && dev < 64;
+  if (slot && (n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  if (slot) known[dev].store(n, std::memory_order_relaxed);
+  return n;
 }
 
 int check_launch(const char* what) {

@@ -23,6 +23,10 @@ int need(const void* p, const char* name);
 int need_aligned(const void* p, const char* name);      // NULL allowed
 int need_dtype_float(int dtype, const char* name);
 
+// Compute units of the current device (256 when the query fails), asked of the
+// runtime once per device.
+int device_cus();
+
 // Checks the launch that was just enqueued.
 int check_launch(const char* what);
 

@@ -610,11 +610,7 @@ RowArgs row_args(const moe_layer* L, const int32_t* offsets, int T, int k, int l
 
 // Persistent grid unit: one block per compute unit, a multiple of the XCD count.
 int persistent_blocks() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    n = 256;
-  n = (n / N_XCD) * N_XCD;
+  const int n = device_cus() / N_XCD * N_XCD;
   return n < N_XCD ? N_XCD : n;
 }
 

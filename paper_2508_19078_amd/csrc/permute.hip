@@ -567,15 +567,6 @@ int check_tk(int T, int k) {
   else if ((k) <= 8) { MACRO(8); }   \
   else { MACRO(16); }
 
-// Compute units of the current device (256 on MI355X when the query fails).
-int cu_count() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    n = 256;
-  return n;
-}
-
 }  // namespace
 }  // namespace fm
 
@@ -673,7 +664,7 @@ int permute_launch(const void* X, int dtype, const int32_t* idx, const float* ga
   if (!one && !fuse) hipLaunchKernelGGL(k_perm_scan, dim3(1), dim3(1024), 0, st, bc, nblk, S_routed, offsets);
   const int row_bytes = d * esize(dtype);
   // 32-token blocks once they fill every compute unit, else 16-token ones
-  const bool wide = cdiv(T, 32) >= cu_count();
+  const bool wide = cdiv(T, 32) >= device_cus();
 #define FM_PS(KM, SC, TOK)                                                                                  \
   hipLaunchKernelGGL((k_place_scatter<KM, SC, TOK>), dim3(cdiv(T, TOK)), dim3(PS_THREADS), 0, st, idx, gate, \
                      expert_map, T, k, S_routed, bc, nblk, offsets, perm_token, perm_gate, inv,             \

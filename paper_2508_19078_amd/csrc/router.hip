@@ -942,21 +942,13 @@ __global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ W, int E
   }
 }
 
-int route_cu_count() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    n = 256;
-  return n;
-}
-
 template <typename TX, typename TW, int MODE>
 int launch_route(const TX* X, const TW* W, const float* ws, const float* bias, int T, int d,
                  int E, int k, int32_t* idx, float* gate, float* logits, int32_t* counts,
                  hipStream_t st) {
   dim3 grid(cdiv(T, RT_TOK));
   if constexpr (std::is_same<TX, bf16>::value) {
-    const int ncu = route_cu_count();
+    const int ncu = device_cus();
     const bool wide = T >= 64 * ncu;
     const bool wider = T >= 128 * ncu;
     // the int8 profiling router keeps the 32-token kernel below when tiles are
