@@ -564,6 +564,7 @@ template <class C> long long max_row_tiles(const RowArgs& ra) {
 
 using F64 = TileCfg<float, 64, 64, 2, 2, 1, 2, 4>;
 using F32 = TileCfg<float, 32, 64, 1, 2, 2, 4, 3>;
+using FD32 = TileCfg<float, 64, 32, 2, 1, 2, 4, 3>;   // weight gradients, few tiles
 using B32 = TileCfg<bf16, 32, 64, 1, 2, 2, 4, 3>;
 using B64 = TileCfg<bf16, 64, 128, 2, 2, 1, 3, 2>;
 using B128 = TileCfg<bf16, 128, 128, 2, 2, 1, 2, 2>;
@@ -589,7 +590,10 @@ template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
     fn(B128{});
   }
 }
-// Weight gradients, each product by its 128 x 128 tiles (every slot counted as
+// fp32 products with fewer than two 64 x 64 tiles per compute unit split k over
+// two waves on 64 x 32 tiles (backward at T = 2000, d = 256, I = 128, 8 slots: 83
+// -> 63 us).
+// bf16 weight gradients, each product by its 128 x 128 tiles (every slot counted as
 // tuning): 64 x 128 tiles with whole slabs where those would be fewer than five
 // per compute unit.  us on 64 x 128, 128 x 128: I = 512, d = 768, 32 slots, r =
 // 512: dW_down (768 tiles) 50, 59, dW_gate/up (1536) 80, 77; r = 128 22, 24 and
@@ -597,9 +601,13 @@ template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
 // 123; I = 376, d = 712, 32 slots, r = 375 (576, 1152) 35, 40 and 52, 55; I =
 // 1408, d = 2048, 64 slots, r = 96 114, 99 and 250, 187.
 template <class Fn> void with_dw(int dtype, long long tiles128, Fn fn) {
-  if (dtype == MOE_F32) fn(F64{});
-  else if (tiles128 < 1280) fn(B64{});
-  else fn(D128{});
+  if (dtype == MOE_F32) {
+    if (4 * tiles128 < 512) fn(FD32{});
+    else fn(F64{});
+  } else {
+    if (tiles128 < 1280) fn(B64{});
+    else fn(D128{});
+  }
 }
 
 RowArgs row_args(const moe_layer* L, const int32_t* offsets, int T, int k, int ldA) {
@@ -628,8 +636,14 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   // T = 64 (1408 tiles) 165 against 169, at r = 31 with 1452 tiles 283 against 249.
   const bool few = r <= 32 && active * ((wide + 127) / 128) < 1024;
   if (L->dtype == MOE_F32) {
-    // r = 7.5 (60 tokens, d = 712, I = 376, 32 slots): fwd 36 against 51 us
-    p.rows = few ? TilePlan::ROWS_32 : TilePlan::ROWS_64;
+    // r = 7.5 (60 tokens, d = 712, I = 376, 32 slots): fwd 36 against 51 us.  Also
+    // where the 64 x 64 tiles are fewer than two per compute unit: a tile's k loop is
+    // then a chain of MFMAs that the 32-row tile's waves share two ways.  Forward
+    // and backward us on 64, 32 rows: T = 256, d = 768, I = 600, 16 slots, k = 4 (456
+    // tiles) 62, 47 and 120, 90; T = 500, d = I = 512, 8 slots, k = 2 (314) 40, 37 and
+    // 84, 82; T = 256, d = 128, I = 256, 6 slots (90) 18, 18 and 42, 36.
+    const bool idle = S * (r / 64 + 0.5) * ((wide + 63) / 64) < 512;
+    p.rows = few || idle ? TilePlan::ROWS_32 : TilePlan::ROWS_64;
     p.dw = TilePlan::SMALL_DW;
     return p;
   }

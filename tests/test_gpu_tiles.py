@@ -38,7 +38,8 @@ CASES = [
     _w(700, 136, 4, 2, 72),                    # r = 350: large tile, 64-row dW tile
     _w(2, 40, 4, 1, 24, "f32"),                # fp32, empty slots, k below one slab
     _w(40, 136, 8, 4, 72, "f32", ns=1),        # r = 22: 32-row tile
-    _w(300, 1032, 5, 3, 264, "f32", bias="zipf"),   # r = 180: 64-row tile
+    _w(300, 1032, 5, 3, 264, "f32", bias="zipf"),   # r = 180, few tiles: 32-row tile, 64-row and split-k dW tiles
+    _w(1200, 264, 16, 4, 520, "f32"),          # r = 300: 64-row tile
 ]
 
 
