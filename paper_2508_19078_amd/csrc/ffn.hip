@@ -931,7 +931,9 @@ static int norm_parts(const moe_layer* L, int T, int k) {
 }
 
 // Backward workspace: schedule | dA_g | dA_u | per-row norm partials (float2) |
-// the utility's per-row values (double).
+// the utility's per-row values (double).  The partials' place is sized for the
+// narrowest dH column tile of any plan (64), so that a workspace sized for T tokens
+// and top-k serves every call with fewer, whichever tiles that call takes.
 struct BwdWs {
   char* dAg;
   char* dAu;
@@ -946,6 +948,9 @@ static int act_ld(const moe_layer* L) { return L->dtype == MOE_BF16 ? (L->I + 63
 static size_t bwd_act_bytes(const moe_layer* L, int T, int k) {
   return round256(rows_total(L, T, k) * act_ld(L) * esize(L->dtype));
 }
+static size_t bwd_norm_bytes(const moe_layer* L, int T, int k) {
+  return round256(sizeof(float2) * rows_total(L, T, k) * cdiv(L->I, NORM_COLS_MIN));
+}
 static BwdWs bwd_ws_at(void* ws, const moe_layer* L, int T, int k) {
   BwdWs w;
   const size_t act = bwd_act_bytes(L, T, k);
@@ -954,15 +959,14 @@ static BwdWs bwd_ws_at(void* ws, const moe_layer* L, int T, int k) {
   w.dAu = p + act;
   p += 2 * act;
   w.norms = (float2*)p;
-  p += round256(sizeof(float2) * rows_total(L, T, k) * norm_parts(L, T, k));
+  p += bwd_norm_bytes(L, T, k);
   w.vrow = (double*)p;
   return w;
 }
 
 extern "C" size_t moe_grouped_swiglu_bwd_workspace_size(const moe_layer* L, int T, int k) {
   if (!L || T < 0 || k <= 0) return 0;
-  return sched_bytes(n_slots(L)) + 2 * bwd_act_bytes(L, T, k) +
-         round256(sizeof(float2) * rows_total(L, T, k) * norm_parts(L, T, k)) +
+  return sched_bytes(n_slots(L)) + 2 * bwd_act_bytes(L, T, k) + bwd_norm_bytes(L, T, k) +
          round256(sizeof(double) * rows_total(L, T, k));
 }
 

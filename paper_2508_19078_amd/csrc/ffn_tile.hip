@@ -244,6 +244,7 @@ __global__ __launch_bounds__(256, C::BPC) void kt_dh(LayerPtrs<typename C::T> W,
   using S = Stage<T, C::RB>;
   constexpr int V = C::V, CH = S::CPR, PER = C::RA * CH / 256, G = PER < 4 ? PER : 4;
   static_assert(C::RA * CH % 256 == 0 && PER % G == 0, "whole chunks per lane");
+  static_assert(C::RB >= NORM_COLS_MIN, "the norm partials' place in the workspace");
   const int d = ra.d, I = ra.I, NT = (I + C::RB - 1) / C::RB;
   tile_sched(pre, wsum, ra, C::RA);
   const Span sp = row_span(pre, ra, NT);

@@ -15,6 +15,7 @@ struct TilePlan {
 TilePlan tile_plan(const moe_layer* L, int T, int k);
 // Columns of I per partial of the utility's row norms (the dH column tile).
 int tile_norm_cols(const moe_layer* L, const TilePlan& p);
+constexpr int NORM_COLS_MIN = 64;   // the fewest that any plan takes
 
 void tile_fwd(const TilePlan& p, const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int T,
               int k, void* Ag, void* Au, void* H, void* O, hipStream_t st);

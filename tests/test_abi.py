@@ -328,3 +328,17 @@ def test_noalloc_permute_rejects_tables_above_its_scratch(L):
     rc, msg = rc_and_msg(L, "moe_permute_noalloc", FAKE, api.MOE_BF16, FAKE, FAKE, FAKE, 64, 256, 256, 17, S, FAKE,
                          FAKE, FAKE, FAKE, FAKE, None, None)
     assert rc == api.MOE_ERR_UNSUPPORTED                             # k > 16: validated as moe_permute does
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,I,S,ns,k", [(2048, 1408, 40, 2, 6), (4096, 688, 16, 0, 4), (712, 376, 32, 1, 2)])
+def test_bwd_workspace_serves_fewer_tokens(L, dtype, d, I, S, ns, k):
+    """A workspace sized for T tokens and top-k is enough for every call with fewer,
+    also where that call takes other tiles: the size never falls as T or k grows."""
+    dt = api.MOE_BF16 if dtype == "bf16" else api.MOE_F32
+    lay = ctypes.byref(api.moe_layer(d, I, dt, S, ns, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE))
+    size = [L.moe_grouped_swiglu_bwd_workspace_size(lay, T, k) for T in range(0, 8192)]
+    assert all(a <= b for a, b in zip(size, size[1:]))
+    for T in (1, 64, 500, 2000, 8192):
+        size = [L.moe_grouped_swiglu_bwd_workspace_size(lay, T, kk) for kk in range(1, 17)]
+        assert all(a <= b for a, b in zip(size, size[1:]))
