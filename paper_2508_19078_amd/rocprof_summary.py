@@ -62,7 +62,7 @@ def stats_table(path: str, top: int) -> str:
         tot = sum(float(r["TotalDurationNs"]) for r in ffn) / steps / 1e3
         out.append("")
         out.append(f"grouped SwiGLU fwd+bwd kernels per step (sum of averages over {steps} steps): {tot:.1f} µs")
-    q8 = [r for r in rows if base_name(r["Name"]) in ("kq_gate_up", "kq_down")]
+    q8 = [r for r in rows if base_name(r["Name"]) in ("kt_q8_gate_up", "kt_q8_down")]
     if q8:
         layers = max(int(r["Calls"]) for r in q8)
         tot = sum(float(r["TotalDurationNs"]) for r in q8) / layers / 1e3
