@@ -15,7 +15,7 @@
 // rows, d = 1024, I = 768 (forward + backward 2.87 ms); a step of T = 1023, d =
 // 1000, I = 616, 16 + 1 experts takes 0.68 ms (1.14 with a 128 x 128 tile per
 // compute unit, register-staged, one slab ahead), one of 256 tokens, d = 128, I =
-// 256 113 us (213).  bf16 with few rows per slot: the weights' bytes; at T = 64,
+// 256, 8 experts 73 us (213; 14 launches, the products 48 us of them).  bf16 with few rows per slot: the weights' bytes; at T = 64,
 // d = 2048, I = 1408, 64 slots gate-up streams 738 MB in 97 us (126 on 256-row
 // tiles, which leave one block per compute unit and 9 of 10 rows empty), down 50
 // (75), dH 51 (94), dX 145 (183: k-major rows 4 KB apart share L2 channels).
