@@ -105,14 +105,14 @@ template <typename T> __device__ __forceinline__ float tile_sigm(float z) { retu
 template <> __device__ __forceinline__ float tile_sigm<bf16>(float z) { return sigm_fast(z); }
 
 template <class C> __device__ __forceinline__ AccCoord tile_coord(int i, int j, int q) {
-  const int lane = lane_id(), wave = wave_id();
+  const int lane = lane_id(), wave = tile_wave<C>();
   return AccCoord{tile_row0<C>(wave) + i * 32 + (lane & 31),
                   tile_col0<C>(wave) + j * 32 + 8 * q + 4 * (lane >> 5)};
 }
 
-// Whether this wave holds accumulators after tile_gemm (the waves with wk = 0).
+// Whether this wave holds sums after tile_gemm (of the waves that split k, those with wk = 0).
 template <class C> __device__ __forceinline__ bool tile_holds() {
-  return C::WK == 1 || wave_id() < C::WM * C::WN;
+  return C::WM * C::WN == 4 || tile_wave<C>() < C::WM * C::WN;
 }
 
 // Puts a block's accumulators into LDS as an RA x RB tile of TO.
@@ -566,7 +566,10 @@ template <class C> long long max_row_tiles(const RowArgs& ra) {
 using F64 = TileCfg<float, 64, 64, 2, 2, 1, 2, 4>;
 using F32 = TileCfg<float, 32, 64, 1, 2, 2, 4, 3>;
 using FD32 = TileCfg<float, 64, 32, 2, 1, 2, 4, 3>;   // weight gradients, few tiles
-using B32 = TileCfg<bf16, 32, 64, 1, 2, 2, 4, 3>;
+// Two of its waves multiply and all four move data: what such a tile waits for is
+// its weights.  (k split over two pairs of waves, whose sums met in LDS, gave the same
+// 28 and 15 us for gate-up and down at T = 8, d = 4096, I = 688, 16 slots.)
+using B32 = TileCfg<bf16, 32, 64, 1, 2, 1, 4, 3>;
 using B64 = TileCfg<bf16, 64, 128, 2, 2, 1, 3, 2>;
 using B128 = TileCfg<bf16, 128, 128, 2, 2, 1, 2, 2>;
 using D128 = TileCfg<bf16, 128, 128, 2, 2, 1, 4, 2, 2, 64>;   // weight gradients: half slabs, three in flight
@@ -630,10 +633,10 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   const double active = (double)((long long)T * k < L->S_routed ? (long long)T * k : L->S_routed) + n_sh;
   const long long wide = (2LL * L->I > L->d ? 2LL * L->I : L->d);
   TilePlan p;
-  // Few rows: 32-row tiles (four waves splitting k two ways) make twice the
-  // blocks of the 64 x 128 tile and waste less on absent rows, which counts
-  // while those would not fill the chip twice.  fwd at T = 8: I = 688, d = 4096,
-  // 16 slots 36 against 49 us; I = 1408, d = 2048, 64 slots 83 against 93; at
+  // Few rows: 32-row tiles make twice the blocks of the 64 x 128 tile and waste
+  // less on absent rows, which counts while those would not fill the chip twice.
+  // fwd at T = 8: I = 688, d = 4096, 16 slots 36 against 49 us; I = 1408, d = 2048,
+  // 64 slots 83 against 93; at
   // T = 64 (1408 tiles) 165 against 169, at r = 31 with 1452 tiles 283 against 249.
   const bool few = r <= 32 && active * ((wide + 127) / 128) < 1024;
   if (L->dtype == MOE_F32) {

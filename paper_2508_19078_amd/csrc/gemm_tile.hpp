@@ -4,7 +4,12 @@
 // A block computes an RA x RB tile of C = sum_k A(r, k) B(n, k); its waves
 // form a WM x WN (x WK) grid and each owns MI x NJ 32 x 32 MFMA tiles
 // (v_mfma_f32_32x32x16_bf16, or 4 x v_mfma_f32_32x32x2_f32 per 8 k), operands
-// swapped so that a lane holds groups of four consecutive output columns.
+// swapped so that a lane holds groups of four consecutive output columns.  On a
+// tile with fewer than four 32 x 32 tiles the waves past the grid only move data.
+//
+// bf16 tiles take WK = 1: every output element is one chain of MFMAs over
+// ascending k, as in the large-tile core, so a row's results do not depend on the
+// tile that its call takes.
 //
 // * Slabs of 128 bytes of k per row (64 bf16 or 32 fp32) go global -> LDS with
 //   global_load_lds_dwordx4 into a ring of NS slabs of both operands, NS - 1 of
@@ -32,7 +37,8 @@
 
 namespace fm {
 
-// WM x WN x WK waves (WK: the waves that split each slab's k), NS slabs in the
+// WM x WN x WK waves that multiply (WK: the waves that split each slab's k;
+// where they are fewer than four, the others only move data), NS slabs in the
 // ring, BPC blocks per compute unit (what the ring leaves room for).
 // BE: bytes per B element, sizeof(T) or 1 (int8 codes widened exactly to bf16 as
 // fragments are read; K-contiguous, 64-byte slab rows).
@@ -53,7 +59,8 @@ struct TileCfg {
   static constexpr int A_INS = A_BYTES / 4096, B_INS = RB * BK * BE / 4096;   // DMA instructions per wave and slab
   static constexpr int INS = A_INS + B_INS;
   static constexpr int LDS = NS * SLAB;
-  static_assert(WM * WN * WK == 4 && TM % 32 == 0 && TN % 32 == 0, "4 waves of 32-multiples");
+  static constexpr int MW = WM * WN * WK;             // waves that multiply
+  static_assert((MW == 4 || (MW == 2 && WK == 1)) && TM % 32 == 0 && TN % 32 == 0, "4 waves of 32-multiples");
   static_assert(NS >= 2 && BPC * (LDS + 6 * 1024) <= 160 * 1024 + 5 * 1024 && (NS - 2) * INS < 64, "ring");
   static_assert(KR == 128 || (KR == 64 && sizeof(T) == 2 && BE == 2), "slab rows");
   static_assert(WK == 1 || (WK - 1) * RA * RB * 4 <= LDS, "partial sums");
@@ -300,6 +307,12 @@ __device__ __forceinline__ f32x16_t tile_mma(f32x4_t b, f32x4_t a, f32x16_t c) {
 // The wave's LDS reads are done and the block meets.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// This wave's place among the waves that multiply, those with a place below MW.
+// Blocks that share a compute unit (256 apart) take opposite pairs of waves, and so
+// of SIMDs, when only two multiply.
+template <class C> __device__ __forceinline__ int tile_wave() {
+  return C::MW == 2 ? wave_id() ^ (2 * ((blockIdx.x >> 8) & 1)) : wave_id();
+}
 // First row / column of a wave's sub-tile.  With two waves along a side, blocks
 // that share a compute unit (256 apart) swap them, so that the waves left idle
 // by partial tiles are not all on the same SIMDs.
@@ -343,7 +356,7 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
     tile_barrier();
     return;
   }
-  const int wave = wave_id();
+  const int wave = tile_wave<C>();
   TileDma<T, AKC, C::RA, AI, C::KR> da;
   std::conditional_t<I8, TileDmaI8<C::RB, BI>, TileDma<T, BKC, C::RB, BI, C::KR>> db;
   da.init(A);
@@ -358,7 +371,7 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
   // (fp32, 75 rows per slot, d = 3480, I = 712: forward 1990 -> 1860 us, backward
   // 2655 -> 2555; a branch inside the slab loop instead cost full tiles 5-15 %)
   auto phys = [](int r, bool inter) { return inter ? 32 * (r >> 6) + (r & 31) : r; };
-  const bool works = phys(row0, AI) < A.rows && phys(col0, BI) < B.rows;
+  const bool works = wave < C::MW && phys(row0, AI) < A.rows && phys(col0, BI) < B.rows;
   constexpr int KW = C::KS / C::WK;   // steps per wave and slab
   // steps whose fragments are read ahead (all, where the registers allow)
   constexpr int SB = C::MI * C::NJ >= 8 && KW > 2 ? 2 : KW;

@@ -92,3 +92,43 @@ Q8_CASES = {
 def test_int8_forward(name, monkeypatch):
     monkeypatch.setitem(Q8.CASES, name, Q8_CASES[name])
     Q8.test_quantised_forward(name)
+
+
+def _bf16(rng, *shape, std=1.0):
+    return torch.from_numpy((std * rng.standard_normal(shape)).astype(np.float32)).to(torch.bfloat16).cuda()
+
+
+# rows per slot of a call on 16 slots, d = 200, I = 1032: one for each row tile
+SAME_ROWS = (5, 40, 100, 300)
+
+
+def test_rows_do_not_depend_on_the_tile():
+    """A row's activations, outputs and gradients are the same bits whichever row
+    tile its call takes: a slot's first rows, alone (32-row tiles) and in larger
+    calls (64 and 128-row tiles, the large ones), in one ascending-k sum each."""
+    S, d, I, n_max = 16, 200, 1032, max(SAME_ROWS)
+    rng = np.random.default_rng([77, d, I])
+    Wg, Wu, Wd = _bf16(rng, S, I, d, std=d ** -0.5), _bf16(rng, S, I, d, std=d ** -0.5), _bf16(rng, S, d, I, std=I ** -0.5)
+    X, dO = _bf16(rng, S, n_max, d), _bf16(rng, S, n_max, d)
+    tables = api.LayerTables(d, I, torch.bfloat16, S, 0, *([m[s] for s in range(S)] for m in (Wg, Wu, Wd)),
+                             *([None] * S for _ in range(3)), device="cuda")
+
+    def call(n):
+        T = S * n
+        e = lambda c: torch.full((T, c), float("nan"), dtype=torch.bfloat16, device="cuda")
+        u8 = lambda b: torch.empty(b, dtype=torch.uint8, device="cuda")
+        off = torch.arange(0, T + 1, n, dtype=torch.int32, device="cuda")
+        Xp, dOp = (t[:, :n].reshape(T, d).contiguous() for t in (X, dO))
+        out = {"A_g": e(I), "A_u": e(I), "H": e(I), "O": e(d), "dX": e(d)}
+        api.moe_grouped_swiglu_fwd(tables, Xp, Xp, off, T, 1, out["A_g"], out["A_u"], out["H"], out["O"],
+                                   u8(api.moe_grouped_swiglu_fwd_workspace_size(tables, T, 1)))
+        api.moe_grouped_swiglu_bwd(tables, Xp, Xp, off, T, 1, out["A_g"], out["A_u"], out["H"], dOp, out["dX"],
+                                   False, u8(api.moe_grouped_swiglu_bwd_workspace_size(tables, T, 1)))
+        torch.cuda.synchronize()
+        return {q: t.view(S, n, -1)[:, :SAME_ROWS[0]] for q, t in out.items()}
+
+    want = call(n_max)
+    for n in SAME_ROWS[:-1]:
+        log(f"{n} rows per slot")
+        for q, t in call(n).items():
+            assert torch.equal(t, want[q]), (n, q)
