@@ -457,8 +457,10 @@ __global__ __launch_bounds__(256, C::BPC) void kt_dw_d(LayerPtrs<typename C::T> 
 }
 
 // The int8 forward: H = silu(s_g (X_s Q_g^T)) (s_u (X_s Q_u^T)) with the codes
-// interleaved as in kt_gate_up.  A wave's columns are whole gate / up pairs of
-// 32-blocks, so H is formed from its fp32 sums in registers.
+// interleaved as in kt_gate_up.  Where a wave's columns are whole gate / up pairs
+// of 32-blocks, H is formed from its fp32 sums in registers; a wave of one
+// 32-block puts its scaled sums into LDS as fp32 and H is formed on the way out
+// (same values, same operations).
 template <class C>
 __global__ __launch_bounds__(256, C::BPC) void kt_q8_gate_up(Q8Ptrs W, const bf16* __restrict__ X,
                                                              const bf16* __restrict__ Xp, RowArgs ra,
@@ -466,10 +468,12 @@ __global__ __launch_bounds__(256, C::BPC) void kt_q8_gate_up(Q8Ptrs W, const bf1
   __shared__ __align__(16) char lds_[C::LDS];
   __shared__ int pre[MAX_S + 1];
   __shared__ int wsum[4];
-  static_assert(C::NJ % 2 == 0, "gate / up pairs per wave");
+  static_assert(C::WK == 1 && (C::NJ == 1 || C::NJ % 2 == 0), "one 32-block or gate / up pairs per wave");
   FM_LDS char* const lds = (FM_LDS char*)lds_;
   constexpr int CI = C::RB / 2;
   using SG = Stage<bf16, CI>;
+  using SF = Stage<float, C::RB>;
+  static_assert(C::NJ > 1 || C::RA * SF::ROW_BYTES <= C::LDS, "staged sums");
   const int d = ra.d, I = ra.I, NT = (I + CI - 1) / CI;
   tile_sched(pre, wsum, ra, C::RA);
   const Span sp = row_span(pre, ra, NT);
@@ -482,9 +486,37 @@ __global__ __launch_bounds__(256, C::BPC) void kt_q8_gate_up(Q8Ptrs W, const bf1
     B16Acc<C::MI, C::NJ> acc;
     acc.zero();
     tile_gemm<C, true, true, false, true>(A, B, d, lds, acc);
-    if (tile_holds<C>()) {
-      const float* const sg = ld_scalar(W.sg + r.s) + n0;
-      const float* const su = ld_scalar(W.su + r.s) + n0;
+    const float* const sg = ld_scalar(W.sg + r.s) + n0;
+    const float* const su = ld_scalar(W.su + r.s) + n0;
+    auto form = [](float a, float u) { return a * sigm_fast(a) * u; };
+    if constexpr (C::NJ == 1) {
+      // rows of RB fp32 values, 32 gate and 32 up columns in turn
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c4 = tile_coord<C>(0, 0, q).col4;
+        const f32x4_t sc = scale4((c4 >> 5) & 1 ? su : sg, 32 * (c4 >> 6) + (c4 & 31), cols);
+#pragma unroll
+        for (int i = 0; i < C::MI; ++i) {
+          const f32x4_t v = acc.quad(i, 0, q);
+          SF::put4(lds, tile_coord<C>(i, 0, q).row, c4, f32x4_t{v[0] * sc[0], v[1] * sc[1], v[2] * sc[2], v[3] * sc[3]});
+        }
+      }
+      barrier_lds_writes();
+      const int tid = wave_id() * 64 + lane_id_here();
+#pragma unroll 2
+      for (int idx = tid; idx < C::RA * SG::CPR; idx += 256) {
+        const int row = idx / SG::CPR, col = idx % SG::CPR * 8, c = 64 * (col >> 5) + (col & 31);
+        float h[8];
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+          const f32x4_t g = *(const FM_LDS f32x4_t*)(lds + SF::at(row, c + e));
+          const f32x4_t u = *(const FM_LDS f32x4_t*)(lds + SF::at(row, c + 32 + e));
+#pragma unroll
+          for (int x = 0; x < 4; ++x) h[e + x] = form(g[x], u[x]);
+        }
+        if (row < r.rows && col < cols) st16(H + (r.ob + row) * I + n0 + col, pack16(h, (bf16*)nullptr));
+      }
+    } else {
 #pragma unroll
       for (int jj = 0; jj < C::NJ / 2; ++jj)
 #pragma unroll
@@ -496,16 +528,13 @@ __global__ __launch_bounds__(256, C::BPC) void kt_q8_gate_up(Q8Ptrs W, const bf1
             const f32x4_t g = acc.quad(i, 2 * jj, q), u = acc.quad(i, 2 * jj + 1, q);
             f32x4_t h;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float a = g[e] * cg[e];
-              h[e] = a * sigm_fast(a) * (u[e] * cu[e]);
-            }
+            for (int e = 0; e < 4; ++e) h[e] = form(g[e] * cg[e], u[e] * cu[e]);
             SG::put4(lds, tile_coord<C>(i, 2 * jj, q).row, col, h);
           }
         }
+      barrier_lds_writes();
+      SG::template copy_out<C::RA, 256>(lds, H + r.ob * I + n0, I, r.rows, cols);
     }
-    barrier_lds_writes();
-    SG::template copy_out<C::RA, 256>(lds, H + r.ob * I + n0, I, r.rows, cols);
     barrier_lds();
   }
 }
@@ -575,10 +604,14 @@ using B128 = TileCfg<bf16, 128, 128, 2, 2, 1, 2, 2>;
 using D128 = TileCfg<bf16, 128, 128, 2, 2, 1, 4, 2, 2, 64>;   // weight gradients: half slabs, three in flight
 
 // int8 weights.  Widening a fragment costs 12 vector instructions, so a wave
-// covers all of the tile's rows (each code is widened once per wave, not once
-// per row of waves): 2 or 4 MFMAs per widened fragment on the 64 and 128-row tiles.
-using Q32 = TileCfg<bf16, 32, 128, 1, 2, 2, 4, 3, 1>;
-using Q64 = TileCfg<bf16, 64, 128, 1, 2, 2, 3, 3, 1>;
+// covers all of the tile's rows (each code is widened once per block, not once
+// per row of waves): 1, 2 or 4 MFMAs per widened fragment on the 32, 64 and
+// 128-row tiles.  The first two give every wave one 32-column block; pairs of
+// waves splitting k over two such blocks were 1-5 % slower (gate-up + down at T =
+// 512, d = 2048, I = 1408, 64 slots, top-6 165 us, now 161; T = 900, d = 768, I =
+// 512, 32 slots, top-5 33.1, now 31.5) and added their sums in another order.
+using Q32 = TileCfg<bf16, 32, 128, 1, 4, 1, 4, 3, 1>;
+using Q64 = TileCfg<bf16, 64, 128, 1, 4, 1, 3, 3, 1>;
 using Q128 = TileCfg<bf16, 128, 256, 1, 4, 1, 2, 2, 1>;
 
 // Calls fn(C{}) with the tile of the plan's row products.

@@ -7,9 +7,9 @@
 // swapped so that a lane holds groups of four consecutive output columns.  On a
 // tile with fewer than four 32 x 32 tiles the waves past the grid only move data.
 //
-// bf16 tiles take WK = 1: every output element is one chain of MFMAs over
-// ascending k, as in the large-tile core, so a row's results do not depend on the
-// tile that its call takes.
+// bf16 tiles never split k (WK = 1): every output element is one chain of MFMAs
+// over ascending k, as in the large-tile core, so a row's results do not depend
+// on the tile that its call takes.
 //
 // * Slabs of 128 bytes of k per row (64 bf16 or 32 fp32) go global -> LDS with
 //   global_load_lds_dwordx4 into a ring of NS slabs of both operands, NS - 1 of
@@ -61,6 +61,7 @@ struct TileCfg {
   static constexpr int LDS = NS * SLAB;
   static constexpr int MW = WM * WN * WK;             // waves that multiply
   static_assert((MW == 4 || (MW == 2 && WK == 1)) && TM % 32 == 0 && TN % 32 == 0, "4 waves of 32-multiples");
+  static_assert(WK == 1 || sizeof(T) == 4, "bf16 sums run over ascending k");
   static_assert(NS >= 2 && BPC * (LDS + 6 * 1024) <= 160 * 1024 + 5 * 1024 && (NS - 2) * INS < 64, "ring");
   static_assert(KR == 128 || (KR == 64 && sizeof(T) == 2 && BE == 2), "slab rows");
   static_assert(WK == 1 || (WK - 1) * RA * RB * 4 <= LDS, "partial sums");

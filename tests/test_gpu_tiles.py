@@ -132,3 +132,31 @@ def test_rows_do_not_depend_on_the_tile():
         log(f"{n} rows per slot")
         for q, t in call(n).items():
             assert torch.equal(t, want[q]), (n, q)
+
+
+def test_int8_rows_do_not_depend_on_the_tile():
+    """The same for the int8 forward's 32, 64 and 128-row tiles (rows per slot 5, 70
+    and 300 on 16 slots, d = 208, I = 1040)."""
+    S, d, I, n_max = 16, 208, 1040, 300
+    rng = np.random.default_rng([78, d, I])
+    q = [torch.from_numpy(rng.integers(-128, 128, size=sh, dtype=np.int8)).cuda() for sh in ((S, I, d), (S, I, d), (S, d, I))]
+    sc = [torch.from_numpy((rng.uniform(0.5, 1.5, size=(S, r)) / (127 * c ** 0.5)).astype(np.float32)).cuda()
+          for r, c in ((I, d), (I, d), (d, I))]
+    X = _bf16(rng, S, n_max, d)
+    tables = api.LayerTablesQ8(d, I, S, 0, *([m[s] for s in range(S)] for m in q + sc), device="cuda")
+
+    def call(n):
+        T = S * n
+        off = torch.arange(0, T + 1, n, dtype=torch.int32, device="cuda")
+        Xp = X[:, :n].reshape(T, d).contiguous()
+        H, Ot = (torch.full((T, c), float("nan"), dtype=torch.bfloat16, device="cuda") for c in (I, d))
+        ws = torch.empty(api.moe_grouped_swiglu_fwd_q8_workspace_size(tables, T, 1), dtype=torch.uint8, device="cuda")
+        api.moe_grouped_swiglu_fwd_q8(tables, Xp, Xp, off, T, 1, H, Ot, ws)
+        torch.cuda.synchronize()
+        return H.view(S, n, I)[:, :5], Ot.view(S, n, d)[:, :5]
+
+    want = call(n_max)
+    for n in (5, 70):
+        log(f"{n} rows per slot")
+        H, Ot = call(n)
+        assert torch.equal(H, want[0]) and torch.equal(Ot, want[1]), n
