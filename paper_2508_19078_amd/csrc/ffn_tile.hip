@@ -637,12 +637,16 @@ template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
 // 40, 34; I = 256, d = 512, 16 slots, r = 2048 (128, 256 tiles) 66, 112 and 79,
 // 123; I = 376, d = 712, 32 slots, r = 375 (576, 1152) 35, 40 and 52, 55; I =
 // 1408, d = 2048, 64 slots, r = 96 114, 99 and 250, 187.
-template <class Fn> void with_dw(int dtype, long long tiles128, Fn fn) {
+DwTile dw_tile_of(int dtype, long long tiles128) {
+  if (dtype == MOE_F32) return 4 * tiles128 < 512 ? DW_SPLIT_K : DW_64;
+  return tiles128 < 1280 ? DW_64 : DW_128;
+}
+template <class Fn> void with_dw(DwTile t, int dtype, Fn fn) {
   if (dtype == MOE_F32) {
-    if (4 * tiles128 < 512) fn(FD32{});
+    if (t == DW_SPLIT_K) fn(FD32{});
     else fn(F64{});
   } else {
-    if (tiles128 < 1280) fn(B64{});
+    if (t == DW_64) fn(B64{});
     else fn(D128{});
   }
 }
@@ -669,8 +673,8 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   // Few rows: 32-row tiles make twice the blocks of the 64 x 128 tile and waste
   // less on absent rows, which counts while those would not fill the chip twice.
   // fwd at T = 8: I = 688, d = 4096, 16 slots 36 against 49 us; I = 1408, d = 2048,
-  // 64 slots 83 against 93; at
-  // T = 64 (1408 tiles) 165 against 169, at r = 31 with 1452 tiles 283 against 249.
+  // 64 slots 83 against 93; at T = 64 (1408 tiles) 165 against 169, at r = 31 with
+  // 1452 tiles 283 against 249.
   const bool few = r <= 32 && active * ((wide + 127) / 128) < 1024;
   if (L->dtype == MOE_F32) {
     // r = 7.5 (60 tokens, d = 712, I = 376, 32 slots): fwd 36 against 51 us.  Also
@@ -684,30 +688,53 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
     p.dw = TilePlan::SMALL_DW;
     return p;
   }
-  // Row products, the sum of gate-up, down, dH and dX in us on 64 x 128, 128 x
-  // 128 and the large tiles (d = 2048, I = 1408, 64 slots unless said): r = 72
-  // 603, 604, 678; r = 96 678, 627, 699; r = 144 846, 751, 769; r = 192 980, 874,
-  // 855.  d = 4096, I = 688, 16 slots: r = 128 245, 285, 311; r = 194 333, 315,
-  // 347; r = 256 398, 334, 370; r = 512 628, 505, 461.  So the large tiles need
-  // slots of about 176 rows, or 288 where they would not fill the chip twice;
-  // 128-row tiles lose below about 88 rows and where they leave half of the
-  // 512 blocks idle.
-  const double mt128 = S * (r / 128 + 0.5), mt256 = S * (r / 256 + 0.5);
-  const double nt_gu = (L->I + 63) / 64, nt_gu256 = (L->I + 127) / 128;
+  // Row products.  A large tile pays where its slots have the rows to fill it, its
+  // layer the tiles to fill the chip and its k loops the length to hide a tile's ends
+  // (one block per compute unit): the line follows r sqrt(S d I).  Below it the 64 x
+  // 128 tile serves short buckets, and layers whose 128-row tiles would leave half of
+  // the 512 blocks of the narrower of gate-up and down idle; 128 x 128 the rest.
+  // Above 288 rows per slot only layers with idle chips lost on the large tiles.
+  // us of forward + backward (the same weight-gradient tiles) on 64 x 128, 128 x 128
+  // and the large tiles, buckets of a skewed router (even: equal popularity):
+  //   S, d, I             r    64    128   large      r    64    128   large
+  //   8, 1024, 2816      160  242    303    278      240  293    319    327
+  //   16, 4096, 688      128  398    441    471      272  601    542    563
+  //   64, 4096, 256       88  505    543    581      240  860    828    805
+  //   32, 4096, 1024      88  931    962   1009      208  1334  1299   1198
+  //   24, 3072, 1536      72  722    746    822      176  1014  1022    958
+  //   64, 2048, 1408      72  1120  1108   1153      144  1377  1297   1289
+  //     even              64  1072  1054   1081      144  1462  1447   1337
+  //   128, 4096, 1408     72  4091  3868   3863      144  4952  4554   4276
+  // The line lies at r^2 S d I = 2.5e12; the one between 64 and 128 at 0.7e12, or at
+  // 0.9e12 while a 128-row tile would be a third empty (r <= 88).
+  const double work = r * r * S * L->d * L->I;
+  const double mt128 = S * (r / 128 + 0.5);
+  const int nt128 = (L->d + 127) / 128 < (L->I + 63) / 64 ? (L->d + 127) / 128 : (L->I + 63) / 64;
   if (few) p.rows = TilePlan::ROWS_32;
-  else if (r <= 88 || (r <= 176 && mt128 * nt_gu <= 288)) p.rows = TilePlan::ROWS_64;
-  else if (r <= 176 || (r <= 288 && mt256 * nt_gu256 < 512)) p.rows = TilePlan::ROWS_128;
-  else p.rows = TilePlan::LARGE_ROWS;
-  // Weight gradients, dW_down + dW_gate/up in us on the tiles of with_dw and on
-  // the large ones: they need slots of about 288 rows and four tiles per compute
-  // unit (every slot counted as tuning) to gain from the large tiles.  I = 1408,
-  // d = 2048, 64 slots: r = 48 144, 157; r = 144 317, 343; r = 288 413, 423; r =
-  // 768 1625, 1181.  I = 688, d = 4096, 16 slots: r = 128 168, 171; r = 256 203, 214;
-  // r = 1024 487, 424.  I = 512, d = 768, 32 slots (384 large tiles): r = 512 127,
-  // 173; r = 1024 198, 264.  I = 256, d = 512, 16 slots: r = 2048 145, 323.
+  else if (r > 288 || work >= 2.5e12) p.rows = TilePlan::LARGE_ROWS;
+  else if (work < (r <= 88 ? 0.9e12 : 0.7e12) || mt128 * nt128 <= 288) p.rows = TilePlan::ROWS_64;
+  else p.rows = TilePlan::ROWS_128;
+  // Weight gradients, us of the backward on the tiles of with_dw and on the large
+  // ones.  The large ones need four tiles per compute unit (every slot counted as
+  // tuning), and slots of about 256 rows: I = 1408, d = 2048, 64 slots r = 176 1065,
+  // 1095; r = 272 1266, 1272; r = 340 1408, 1352; I = 688, d = 4096, 16 slots r = 176
+  // 376, 380; r = 304 427, 424.  About 100 rows are enough where I is a multiple of 256
+  // and d >= 3072 (the small tiles read half lines, here of rows a multiple of 512
+  // bytes apart): I = 1024, 32 slots r = 112 760, 730, r = 240 967, 868; I = 256, d =
+  // 4096, 64 slots r = 240 592, 542; I = 1536, d = 3072, 24 slots r = 112 648, 657, r =
+  // 240 779, 751; and in the widest layers (d = 4096, I = 1408, 128 slots: r = 112
+  // 3362, 3372; r = 240 4592, 4276).
+  // Too few tiles (large, small, for dW_down + dW_gate/up): I = 512, d = 768, 32 slots
+  // (384) r = 512 173, 127; I = 256, d = 512, 16 slots r = 2048 323, 145.
   const double dw256 = (double)S * ((L->I + 127) / 128) * ((L->d + 255) / 256);
-  p.dw = r > 288 && dw256 >= 1024 ? TilePlan::LARGE_DW : TilePlan::SMALL_DW;
+  const bool dw_early = dw256 >= 8192 || (L->I % 256 == 0 && L->d >= 3072);
+  p.dw = dw256 >= 1024 && r > (dw_early ? 100 : 256) ? TilePlan::LARGE_DW : TilePlan::SMALL_DW;
   return p;
+}
+
+DwTile dw_tile(const moe_layer* L, bool gate_up) {
+  const long long S = L->S_routed + L->S_shared;
+  return dw_tile_of(L->dtype, S * cdiv(L->d, 128) * cdiv(L->I, gate_up ? 64 : 128));
 }
 
 int tile_norm_cols(const moe_layer* L, const TilePlan& p) {
@@ -755,14 +782,13 @@ void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int 
 void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int Tn, int k, const void* H,
              const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate, hipStream_t st) {
   const RowArgs ra = row_args(L, offsets, Tn, k, ldA);
-  const long long nd = cdiv(ra.d, 128);
-  with_dw(L->dtype, ra.S * nd * cdiv(ra.I, 128), [&](auto c) {
+  with_dw(dw_tile(L, false), L->dtype, [&](auto c) {
     typedef decltype(c) C;
     typedef typename C::T T;
     hipLaunchKernelGGL(kt_dw_d<C>, tile_grid<C>((long long)ra.S * cdiv(ra.d, C::RA) * cdiv(ra.I, C::RB)), dim3(256), 0,
                        st, layer_ptrs<T>(L), (const T*)dO, (const T*)H, ra, accumulate);
   });
-  with_dw(L->dtype, ra.S * nd * cdiv(ra.I, 64), [&](auto c) {
+  with_dw(dw_tile(L, true), L->dtype, [&](auto c) {
     typedef decltype(c) C;
     typedef typename C::T T;
     hipLaunchKernelGGL(kt_dw_gu<C>, tile_grid<C>((long long)ra.S * cdiv(ra.I, C::RA / 2) * cdiv(ra.d, C::RB)),

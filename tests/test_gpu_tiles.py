@@ -32,8 +32,8 @@ CASES = [
     _w(33, 200, 6, 2, 136, ns=1),              # r = 14
     _w(130, 264, 8, 4, 136),                   # r = 65: 64-row tile
     _w(150, 136, 4, 2, 24, ns=1),              # r = 90 but few tiles: 64-row tile
-    _w(800, 1032, 64, 8, 264),                 # r = 100: 128-row tile, 128-row dW tile
-    _w(1600, 520, 64, 8, 776, bias="zipf"),    # r = 200, large d, 128-row dW tiles
+    _w(800, 1032, 64, 8, 264),                 # r = 100: 64-row tile, 128-row dW tile
+    _w(1600, 520, 64, 8, 776, bias="zipf"),    # r = 200: 128-row tile, 128-row dW tiles
     _w(2400, 520, 64, 8, 776),                 # r = 300: large tiles throughout
     _w(700, 136, 4, 2, 72),                    # r = 350: large tile, 64-row dW tile
     _w(2, 40, 4, 1, 24, "f32"),                # fp32, empty slots, k below one slab
@@ -98,15 +98,17 @@ def _bf16(rng, *shape, std=1.0):
     return torch.from_numpy((std * rng.standard_normal(shape)).astype(np.float32)).to(torch.bfloat16).cuda()
 
 
-# rows per slot of a call on 16 slots, d = 200, I = 1032: one for each row tile
-SAME_ROWS = (5, 40, 100, 300)
+# rows per slot of a call on 32 slots, d = 712, I = 1032: one for each row tile
+SAME_ROWS = {5: "32", 40: "64", 200: "128", 300: "large"}
+SAME_LAYER = dict(S=32, d=712, I=1032)
 
 
 def test_rows_do_not_depend_on_the_tile():
     """A row's activations, outputs and gradients are the same bits whichever row
     tile its call takes: a slot's first rows, alone (32-row tiles) and in larger
     calls (64 and 128-row tiles, the large ones), in one ascending-k sum each."""
-    S, d, I, n_max = 16, 200, 1032, max(SAME_ROWS)
+    S, d, I = (SAME_LAYER[q] for q in "SdI")
+    n_min, n_max = min(SAME_ROWS), max(SAME_ROWS)
     rng = np.random.default_rng([77, d, I])
     Wg, Wu, Wd = _bf16(rng, S, I, d, std=d ** -0.5), _bf16(rng, S, I, d, std=d ** -0.5), _bf16(rng, S, d, I, std=I ** -0.5)
     X, dO = _bf16(rng, S, n_max, d), _bf16(rng, S, n_max, d)
@@ -125,10 +127,10 @@ def test_rows_do_not_depend_on_the_tile():
         api.moe_grouped_swiglu_bwd(tables, Xp, Xp, off, T, 1, out["A_g"], out["A_u"], out["H"], dOp, out["dX"],
                                    False, u8(api.moe_grouped_swiglu_bwd_workspace_size(tables, T, 1)))
         torch.cuda.synchronize()
-        return {q: t.view(S, n, -1)[:, :SAME_ROWS[0]] for q, t in out.items()}
+        return {q: t.view(S, n, -1)[:, :n_min] for q, t in out.items()}
 
     want = call(n_max)
-    for n in SAME_ROWS[:-1]:
+    for n in sorted(SAME_ROWS)[:-1]:
         log(f"{n} rows per slot")
         for q, t in call(n).items():
             assert torch.equal(t, want[q]), (n, q)
