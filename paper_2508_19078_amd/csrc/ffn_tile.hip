@@ -797,21 +797,29 @@ void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* o
   });
 }
 
-// The int8 forward's tile, from the average rows per slot r and the tiles (time
-// of gate-up + down in us on the 32, 64 and 128-row tile; in brackets the
-// 256-row, 8-wave tile the int8 forward used before, with the same widening).
-// d = 2048, I = 1408, 64 slots: r = 6 96, 93, 121 [179]; r = 24 142, 135, 156
-// [233]; r = 48 190, 162, 185 [252]; r = 96 274, 225, 218 [319]; r = 384 925, 659,
-// 526 [575]; r = 768 1728, 1218, 912 [966].  d = 4096, I = 688, 16 slots: r = 2 48,
-// 54, 92 [106]; r = 64 65, 69, 99 [116]; r = 194 (192 128-row tiles) 133, 104, 125
-// [149]; r = 375 (330 tiles) 242, 170, 162 [191]; r = 1024 623, 429, 358 [369].  d =
-// 768, I = 512, 32 slots: r = 2 20, 23, 34 [43]; r = 128 40, 33, 38 [60]; r = 512
-// 107, 77, 68 [93].
+// Rows of the int8 forward's row tile, from the average rows per slot r and the tiles:
+// 32, 64 and 128 on the core of this file, 256 on the 8-wave tile of ffn.hip.  us of
+// gate-up + down on each.  d = 2048, I = 1408, 64 slots: r = 6 94, 92, 120, 186; r = 24
+// 144, 132, 155, 241; r = 48 191, 161, 184, 257; r = 96 283, 223, 211, 329; r = 384 930,
+// 633, 523, 567.  d = 4096, I = 688, 16 slots: r = 2 45, 50, 89, 101; r = 64 64, 67, 98,
+// 111; r = 194 (192 128-row tiles) 134, 101, 118, 151; r = 375 (330 tiles) 249, 167,
+// 164, 191; r = 1024 622, 432, 357, 359.  d = 768, I = 512, 32 slots: r = 2 17, 19, 33,
+// 38; r = 128 37, 29, 37, 57; r = 512 100, 72, 67, 90.
+// The 256-row tile moves 3/4 of the bytes per product and holds one block per compute
+// unit, so it needs many rows and large layers (r^2 S d I, as the bf16 row products),
+// us on 128, 256 rows: 64 slots, d = 2048, I = 1408 r = 512 615, 645; r = 1024 1174,
+// 1146; r = 4096 4665, 4278; d = 4096, I = 1024 r = 4096 6945, 6203; d = 1024, I = 2816 r
+// = 768 944, 971; r = 2048 2395, 2363; 8 slots, d = 4096, I = 2816 r = 512 290, 305; r =
+// 2048 1034, 996; r = 8192 4286, 3822.  Layers of few or short products never gained:
+// 16 slots, d = 4096, I = 688 r = 2048 638, 690; r = 8192 2457, 2448; 32 slots, d = 1024,
+// I = 512 r = 8192 936, 981.
 int q8_tile(const moe_layer_q8* L, int T, int k) {
   const int S = L->S_routed + L->S_shared;
   const double r = (double)T * (k + L->S_shared) / S;
   const double active = (double)((long long)T * k < L->S_routed ? (long long)T * k : L->S_routed) + L->S_shared;
   if (r <= 64 && active * ((2LL * L->I + 127) / 128) < 768) return 32;
+  const double layer = (double)S * L->d * L->I;
+  if (layer >= 5e7 && r * r * layer >= 1.5e14) return 256;
   return r >= 72 && S * (r / 128 + 0.5) * ((L->I + 127) / 128) >= 288 ? 128 : 64;
 }
 
@@ -830,7 +838,7 @@ void tile_fwd_q8(const moe_layer_q8* L, const void* X, const void* Xp, const int
   switch (q8_tile(L, Tn, k)) {
     case 32: run(Q32{}); break;
     case 64: run(Q64{}); break;
-    default: run(Q128{}); break;
+    default: run(Q128{}); break;   // q8_tile(L, Tn, k) < 256
   }
 }
 

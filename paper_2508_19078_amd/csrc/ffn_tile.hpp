@@ -31,7 +31,9 @@ void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* o
 void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int T, int k, const void* dAg,
              const void* dAu, int ldA, void* dXp, hipStream_t st);
 
-// The int8 forward.
+// Rows of the int8 forward's row tile: 32, 64, 128, or 256 (the kernels of ffn.hip).
+int q8_tile(const moe_layer_q8* L, int T, int k);
+// The int8 forward on a tile of fewer than 256 rows.
 void tile_fwd_q8(const moe_layer_q8* L, const void* X, const void* Xp, const int32_t* offsets, int T, int k, void* H,
                  void* O, hipStream_t st);
 

@@ -204,51 +204,6 @@ template <int R, bool INTER> struct TileDmaI8 {
   }
 };
 
-// Eight int8 codes -> eight bf16 (exact: |q| <= 128 has at most 8 significant
-// bits).  One SDWA conversion per code straight from its byte, one byte permute
-// per pair of high halves: 12 instructions.  Written out because the compiler
-// turned the shifts of plain C++ into 28 (shift, sign-extending extract,
-// conversion, shift, and-or).
-template <int BYTE> __device__ __forceinline__ uint32_t cvt_code(uint32_t x) {
-  uint32_t f;
-  if constexpr (BYTE == 0)
-    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(f) : "v"(x));
-  else if constexpr (BYTE == 1)
-    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1" : "=v"(f) : "v"(x));
-  else if constexpr (BYTE == 2)
-    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(f) : "v"(x));
-  else
-    asm("v_cvt_f32_i32_sdwa %0, sext(%1) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3" : "=v"(f) : "v"(x));
-  return f;
-}
-__device__ __forceinline__ bf16x8_t widen_i8x8(u32x2_t raw) {
-  u32x4_t v;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    v[2 * i] = __builtin_amdgcn_perm(cvt_code<1>(raw[i]), cvt_code<0>(raw[i]), 0x07060302u);
-    v[2 * i + 1] = __builtin_amdgcn_perm(cvt_code<3>(raw[i]), cvt_code<2>(raw[i]), 0x07060302u);
-  }
-  return __builtin_bit_cast(bf16x8_t, v);
-}
-
-// Fragments of an int8 slab: lane l holds row r0 + l % 32 and k 16 ks +
-// 8 (l / 32) + 0..7, i.e. 8 bytes of chunk ks (swizzled).
-// Sixteen consecutive rows read 16 distinct 2-bank groups.
-template <int R, int NB> struct I8Frag {
-  uint32_t off[NB];
-  __device__ __forceinline__ void init(int row0) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int r = row0 + i * 32 + (lane & 31);
-      off[i] = (uint32_t)(r * 64 + (swz_kc(r) << 4) + 8 * (lane >> 5));
-    }
-  }
-  __device__ __forceinline__ u32x2_t codes(const FM_LDS char* tile, int i, int ks) const {
-    return *(const FM_LDS u32x2_t*)(tile + (off[i] ^ (uint32_t)(ks << 4)));
-  }
-};
-
 template <typename T> struct tile_frag;
 template <> struct tile_frag<bf16> { typedef bf16x8_t type; };
 template <> struct tile_frag<float> { typedef f32x4_t type; };

@@ -85,7 +85,10 @@ Q8_CASES = {
     "tiles_q8_32": (20, 80, 8, 2, 48, 1, 7, None),         # r = 7, an empty slot
     "tiles_q8_64": (260, 144, 6, 2, 112, 0, 6, None),      # r = 87, 12 128-row tiles
     "tiles_q8_128": (1600, 144, 64, 6, 336, 0, 63, None),  # r = 150, 320 128-row tiles; I and d end inside a slab
+    "tiles_q8_256": (7100, 4112, 4, 1, 3056, 0, 4, 96),    # r = 1775, the 256-row tile; I and d end inside a slab
 }
+# rows of each one's row tile
+Q8_TILES = {"tiles_q8_32": 32, "tiles_q8_64": 64, "tiles_q8_128": 128, "tiles_q8_256": 256}
 
 
 @pytest.mark.parametrize("name", list(Q8_CASES))
@@ -136,10 +139,16 @@ def test_rows_do_not_depend_on_the_tile():
             assert torch.equal(t, want[q]), (n, q)
 
 
-def test_int8_rows_do_not_depend_on_the_tile():
-    """The same for the int8 forward's 32, 64 and 128-row tiles (rows per slot 5, 70
-    and 300 on 16 slots, d = 208, I = 1040)."""
-    S, d, I, n_max = 16, 208, 1040, 300
+# layers and rows per slot of the int8 calls compared bit for bit: the row tile of each
+Q8_SAME = [(dict(S=16, d=208, I=1040), {5: 32, 70: 64, 300: 128}),
+           (dict(S=4, d=4112, I=3056), {100: 64, 600: 128, 1750: 256})]
+
+
+@pytest.mark.parametrize("layer,rows", Q8_SAME)
+def test_int8_rows_do_not_depend_on_the_tile(layer, rows):
+    """The same for the int8 forward's row tiles."""
+    S, d, I = (layer[q] for q in "SdI")
+    n_min, n_max = min(rows), max(rows)
     rng = np.random.default_rng([78, d, I])
     q = [torch.from_numpy(rng.integers(-128, 128, size=sh, dtype=np.int8)).cuda() for sh in ((S, I, d), (S, I, d), (S, d, I))]
     sc = [torch.from_numpy((rng.uniform(0.5, 1.5, size=(S, r)) / (127 * c ** 0.5)).astype(np.float32)).cuda()
@@ -155,10 +164,10 @@ def test_int8_rows_do_not_depend_on_the_tile():
         ws = torch.empty(api.moe_grouped_swiglu_fwd_q8_workspace_size(tables, T, 1), dtype=torch.uint8, device="cuda")
         api.moe_grouped_swiglu_fwd_q8(tables, Xp, Xp, off, T, 1, H, Ot, ws)
         torch.cuda.synchronize()
-        return H.view(S, n, I)[:, :5], Ot.view(S, n, d)[:, :5]
+        return H.view(S, n, I)[:, :n_min], Ot.view(S, n, d)[:, :n_min]
 
     want = call(n_max)
-    for n in (5, 70):
+    for n in sorted(rows)[:-1]:
         log(f"{n} rows per slot")
         H, Ot = call(n)
         assert torch.equal(H, want[0]) and torch.equal(Ot, want[1]), n

@@ -25,6 +25,14 @@ def plan(d, I, S, ns, T, k, dtype="bf16"):
     return ROWS[p.rows], DW[p.dw]
 
 
+def q8_rows(d, I, S, ns, T, k):
+    """Rows of the int8 forward's row tile."""
+    f = getattr(api.lib(), "_ZN2fm7q8_tileEPK12moe_layer_q8ii")   # fm::q8_tile(const moe_layer_q8*, int, int)
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    L = api.moe_layer_q8(d, I, S, ns, *[None] * 6)
+    return f(ctypes.addressof(L), T, k)
+
+
 # d, I, slots, rows per slot (T = rows x slots / 4, top-4): row tile, weight gradients
 TIMED = [
     ((4096, 1024, 32, 80), ("64", "small")),
@@ -54,7 +62,35 @@ def test_timed_shapes(shape, want):
     assert plan(d, I, S, 0, r * S // 4, 4) == want
 
 
+# The int8 forward, gate-up + down in us on 128 and 256 rows
+Q8_TIMED = [
+    ((2048, 1408, 64, 512), 128),     # 615, 645
+    ((2048, 1408, 64, 2048), 256),    # 2314, 2214
+    ((2048, 1408, 64, 4096), 256),    # 4665, 4278
+    ((4096, 1024, 64, 4096), 256),    # 6945, 6203
+    ((4096, 2816, 8, 512), 128),      # 290, 305
+    ((4096, 2816, 8, 2048), 256),     # 1034, 996
+    ((4096, 688, 16, 2048), 128),     # 638, 690
+    ((1024, 512, 32, 8192), 128),     # 936, 981
+]
+
+
+@pytest.mark.parametrize("shape,want", Q8_TIMED)
+def test_timed_int8_shapes(shape, want):
+    d, I, S, r = shape
+    assert q8_rows(d, I, S, 0, r * S // 8, 8) == want
+
+
 def test_rows_that_must_not_depend_on_the_tile_cover_every_tile():
     for n, tile in G.SAME_ROWS.items():
         c = G.SAME_LAYER
         assert plan(c["d"], c["I"], c["S"], 0, c["S"] * n, 1)[0] == tile
+    for c, rows in G.Q8_SAME:
+        for n, tile in rows.items():
+            assert q8_rows(c["d"], c["I"], c["S"], 0, c["S"] * n, 1) == tile
+
+
+@pytest.mark.parametrize("name", list(G.Q8_TILES))
+def test_int8_cases_take_their_tile(name):
+    T, d, E, k, I, ns, _, _ = G.Q8_CASES[name]
+    assert q8_rows(d, I, E, ns, T, k) == G.Q8_TILES[name]
