@@ -29,10 +29,14 @@ constexpr int PM_TOK = 256;   // tokens (threads) per block of count/place
 constexpr int PM_SMAX = 512;  // slots count and place support
 constexpr int PM_FUSE = 16384;  // place sums the count table itself up to this many entries
 // Choices (T k) up to which every place block counts all tokens itself instead
-// of reading a count launch's table.  us with and without that launch: T k = 32
-// 9.2, 8.1; 512 6.0, 4.5; 1998 12.2, 10.8; 3108 14.5, 14.2; 4096 6.9, 6.2; 6144
-// 14.0, 14.2; 8192 13.3, 15.8.
-constexpr int PM_ONE = 4096;
+// of reading a count launch's table.  Device us (replayed graph) with and without
+// that launch, equal popularity and Zipf (tokens of one slot meet at one LDS counter,
+// whose atomics then run one by one): d = 512, 4 slots, k = 1 T = 1024 5.6, 4.3 and
+// 5.6, 4.7; T = 2048 5.9, 5.0 and 5.9, 5.8; T = 3072 6.1, 5.8 and 6.1, 7.0; T = 4096
+// 6.2, 6.5 and 6.2, 8.2; d = 2048, 64 slots, k = 6 T = 341 11.9, 10.7 and 12.1, 11.3;
+// T = 680 12.9, 12.8 and 13.0, 13.4; k = 8 T = 256 14.3, 13.2 and 14.6, 13.4; T = 512
+// 15.6, 15.5 and 15.8, 16.4.
+constexpr int PM_ONE = 2048;
 enum { PLACE_POS = 0, PLACE_SCAN = 1, PLACE_ALL = 2 };   // what place gets: row positions, counts, nothing
 constexpr int PS_THREADS = 512;  // place + scatter: 8 waves of 16 or 32 tokens per block
 

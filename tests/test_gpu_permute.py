@@ -1,8 +1,9 @@
 """Gate re-routing and permutation (Section 7) alone, through the C ABI, against
 the oracle's maps, bit-exact: offsets, perm_token and inv exactly, perm_gate to
-fp32 summation order, X_perm rows bit for bit.  The shapes reach both ways the
-entry point builds the maps (each block summing the slots x count-blocks table
-itself up to 16384 entries, a separate scan launch beyond), the
+fp32 summation order, X_perm rows bit for bit.  The shapes reach the three ways the
+entry point builds the maps (each block counting all tokens itself up to 2048
+choices; each block summing the slots x count-blocks table itself up to 16384
+entries; a separate scan launch beyond), the
 largest slot count (512), slot maps that fold several experts into one slot (a
 token's choices merged into one row), maps that leave slots empty, and the
 largest k."""
@@ -24,6 +25,10 @@ CASES = {
     "scan_274_blocks_gaps": (70000, 16, 64, 8, "even", 128, torch.bfloat16),
     "max_slots_k16": (3000, 32, 256, 16, "odd", 512, torch.bfloat16),
     "fp32_ragged": (257, 24, 16, 4, "pairs", 8, torch.float32),
+    # the most choices whose maps one launch makes, and one more
+    "last_one_launch_k1": (2048, 40, 4, 1, "pairs", 2, torch.bfloat16),
+    "last_one_launch_k8": (256, 40, 64, 8, "even", 128, torch.bfloat16),
+    "first_two_launches": (683, 40, 16, 3, "identity", 16, torch.bfloat16),
 }
 
 
