@@ -22,10 +22,15 @@ import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 
-# The kernels of moe_grouped_swiglu_fwd + moe_grouped_swiglu_bwd (bf16 path).
-FFN_KERNELS = ("k_build_sched", "kb_gate_up", "kb_down", "kb_dh", "kb_dx", "kb_dw_gu", "kb_dw_d")
-# Sources those kernels are built from.
-FFN_SOURCES = ("csrc/ffn.hip", "csrc/ffn_common.hpp", "csrc/gemm_bf16.hpp", "csrc/common.hpp")
+# The products of moe_grouped_swiglu_fwd + moe_grouped_swiglu_bwd.  A call takes each
+# on the large tiles (kb_) or the small ones (kt_).
+PRODUCTS = ("gate_up", "down", "dh", "dx", "dw_gu", "dw_d")
+FFN_KERNELS = ("k_build_sched",) + tuple(t + p for t in ("kb_", "kt_") for p in PRODUCTS)
+# Sources those kernels are built from and chosen in.
+FFN_SOURCES = ("csrc/ffn.hip", "csrc/ffn_common.hpp", "csrc/gemm_bf16.hpp", "csrc/ffn_tile.hip", "csrc/ffn_tile.hpp",
+               "csrc/gemm_tile.hpp", "csrc/common.hpp")
+# The int8 forward's, on the 256-row tile and the smaller ones.
+Q8_KERNELS = ("kq_gate_up", "kq_down", "kt_q8_gate_up", "kt_q8_down")
 CALIB_KERNEL = "copyBuffer"
 
 
@@ -47,6 +52,10 @@ def base_name(n: str) -> str:
     return short_name(n).split("<")[0]
 
 
+def is_product(kernel: str, product: str) -> bool:
+    return kernel in ("kb_" + product, "kt_" + product)
+
+
 def stats_table(path: str, top: int) -> str:
     rows = list(csv.DictReader(open(path)))
     # PyTorch's own kernels (input generation, fills) are left out of the table
@@ -56,15 +65,14 @@ def stats_table(path: str, top: int) -> str:
         out.append(f"| {short_name(r['Name'])} | {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | "
                    f"{float(r['TotalDurationNs']) / 1e6:.3f} | {float(r['Percentage']):.1f} |")
     ffn = [r for r in rows if base_name(r["Name"]) in FFN_KERNELS]
-    calls = [int(r["Calls"]) for r in ffn if base_name(r["Name"]) == "kb_gate_up"]
-    if calls:
-        steps = max(calls)
+    steps = sum(int(r["Calls"]) for r in ffn if is_product(base_name(r["Name"]), "gate_up"))
+    if steps:
         tot = sum(float(r["TotalDurationNs"]) for r in ffn) / steps / 1e3
         out.append("")
         out.append(f"grouped SwiGLU fwd+bwd kernels per step (sum of averages over {steps} steps): {tot:.1f} µs")
-    q8 = [r for r in rows if base_name(r["Name"]) in ("kt_q8_gate_up", "kt_q8_down")]
-    if q8:
-        layers = max(int(r["Calls"]) for r in q8)
+    q8 = [r for r in rows if base_name(r["Name"]) in Q8_KERNELS]
+    layers = sum(int(r["Calls"]) for r in q8 if base_name(r["Name"]).endswith("gate_up"))
+    if layers:
         tot = sum(float(r["TotalDurationNs"]) for r in q8) / layers / 1e3
         out.append("")
         out.append(f"int8-code grouped forward kernels per layer (sum of averages over {layers} layer passes): "
@@ -86,7 +94,8 @@ def counter_per_kernel(path: str, counter: str):
 def operand_bytes(rows: dict):
     """Distinct bytes each grouped-SwiGLU kernel must read and write in one step
     (every operand once, no padding): rows['total'] rows over rows['slots']
-    slots with rows, rows['tuning'] rows of rows['tuning_slots'] tuning slots."""
+    slots with rows, rows['tuning'] rows of rows['tuning_slots'] tuning slots; the
+    same on the small tiles as under the large ones' names."""
     n, nt, s, st = rows["total"], rows["tuning"], rows["slots"], rows["tuning_slots"]
     d, I, b = rows["d"], rows["I"], rows["bytes"]
     w = d * I * b                      # one matrix of one slot
@@ -109,7 +118,7 @@ def traffic(fetch_csv: str, write_csv: str, calib_bytes: int):
             raise SystemExit(f"no {CALIB_KERNEL} dispatch in {path}")
         kib = max(calib)
         factor = (calib_bytes / 1024.0) / kib
-        steps = len(per.get("kb_gate_up", []))
+        steps = sum(len(v) for k, v in per.items() if is_product(k, "gate_up"))
         raw = sum(sum(per.get(k, [])) for k in FFN_KERNELS) / max(steps, 1)
         res[name] = {"calib_kib": kib, "factor": factor, "steps": steps, "kib_per_step": raw,
                      "bytes_per_step": raw * 1024.0 * factor,
@@ -159,9 +168,12 @@ def main():
     print("|---|---|---|---|---|---|---|---|---|")
     for k in FFN_KERNELS:
         fr, wr = f["per_kernel_kib"][k], w["per_kernel_kib"][k]
+        if fr == 0 and wr == 0:
+            continue                       # this step took the product's other tiles
         fs, ws_ = fr * 1024 * f["factor"], wr * 1024 * w["factor"]
-        if ops and k in ops:
-            ro, wo = ops[k]
+        product = "kb_" + k[3:]
+        if ops and product in ops:
+            ro, wo = ops[product]
             print(f"| {k} | {fr:.0f} | {fs / 1e6:.1f} | {ro / 1e6:.1f} | {fs / ro:.2f} | {wr:.0f} | {ws_ / 1e6:.1f} | "
                   f"{wo / 1e6:.1f} | {ws_ / wo:.2f} |")
         else:

@@ -97,3 +97,49 @@ def test_stats_table_leaves_out_torch_kernels_and_sums_a_step(tmp_path):
     assert "k_combine<fm::bf16, 8>" in out
     # (4 + 2) ms over 4 steps of the FFN kernels
     assert "over 4 steps): 1500.0 µs" in out
+
+
+TILE = "<fm::TileCfg<fm::bf16, {}, 128, 2, 2, 1, 3, 2, 2, 128> >"
+
+
+def write_stats(path, names):
+    with open(path, "w", newline="") as f:
+        w = csv.DictWriter(f, fieldnames=["Name", "Calls", "TotalDurationNs", "AverageNs", "Percentage"])
+        w.writeheader()
+        for n, c, tot in names:
+            w.writerow({"Name": n, "Calls": c, "TotalDurationNs": tot, "AverageNs": tot / c, "Percentage": 10.0})
+
+
+def test_a_step_on_both_kinds_of_tiles_counts_all_its_kernels(tmp_path):
+    """Large row tiles with small weight-gradient tiles, and steps of small tiles
+    only, of two shapes: every product's time, over the gate-up launches of both."""
+    path = tmp_path / "s.csv"
+    write_stats(path, [(K.format("kb_gate_up"), 2, 4e6), (K.format("kt_dw_gu" + TILE.format(64)), 5, 3e6),
+                       (K.format("kt_dw_d" + TILE.format(64)), 5, 1e6), (K.format("kt_gate_up" + TILE.format(64)), 2, 1e6),
+                       (K.format("kt_gate_up" + TILE.format(32)), 1, 1e6),
+                       (K.format("kt_q8_gate_up" + TILE.format(64)), 3, 2e6), (K.format("kq_gate_up"), 1, 1e6),
+                       (K.format("kq_down"), 1, 1e6)])
+    out = R.stats_table(str(path), 10)
+    assert "over 5 steps): 2000.0 µs" in out
+    assert "over 4 layer passes): 1000.0 µs" in out
+    calib = 1 << 20
+    copy = {"__amd_rocclr_copyBuffer": [[calib / 1024]]}
+    for c in ("FETCH_SIZE", "WRITE_SIZE"):
+        write_counters(tmp_path / c, counter_rows(c, {**copy, "kb_gate_up": [[10], [10]], "kt_gate_up" + TILE.format(64): [[4]],
+                                                      "kt_dw_d" + TILE.format(64): [[6], [6], [6]]}))
+    t = R.traffic(str(tmp_path / "FETCH_SIZE"), str(tmp_path / "WRITE_SIZE"), calib)
+    assert t["FETCH_SIZE"]["steps"] == 3
+    assert t["FETCH_SIZE"]["kib_per_step"] == pytest.approx((20 + 4 + 18) / 3)
+
+
+def test_the_source_hash_covers_every_source_of_the_kernels():
+    """What the products' sources include, and the file that chooses their tiles."""
+    import os
+    import re
+    seen, todo = set(), ["csrc/ffn.hip", "csrc/ffn_tile.hip"]
+    while todo:
+        rel = todo.pop()
+        seen.add(rel)
+        with open(os.path.join(R.PKG, rel)) as f:
+            todo += [p for p in ("csrc/" + m for m in re.findall(r'#include "([a-z0-9_]+\.hpp)"', f.read())) if p not in seen]
+    assert seen - {"csrc/debug.hpp"} == set(R.FFN_SOURCES)   # the debug checks are host code
