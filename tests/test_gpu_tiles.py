@@ -1,7 +1,7 @@
 """The grouped FFN at the sizes where its tile shapes change: each small tile
-(32, 64 and 128 rows), the large one, and both ways to pair them with the
-weight gradients' tiles, and the int8 forward's, at row, column and k remainders (d and I multiples of
-8, a single token, empty tuning slots, shared experts).  A whole step through
+(32, 64 and 128 rows), the large one, every pairing with the weight gradients'
+tiles, and the int8 forward's, at row, column and k remainders (d and I multiples
+of 8, a single token, empty tuning slots, shared experts).  A whole step through
 the C ABI against the fp64 oracle on the oracle's routing."""
 import numpy as np
 import pytest
@@ -26,24 +26,28 @@ def _w(T, d, E, k, I, dtype="bf16", ns=0, bias="normal"):
                            dtype=dtype, n_shared=ns, bias_kind=bias, bias_var=1.0, zipf_s=1.2)
 
 
-# r = T (k + shared) / slots decides the row tile, the weights' size the dW tile
+# r = T (k + shared) / slots and the layer's size decide the row tile and those of
+# dW_down and dW_gate/up, named here as fm::tile_plan and fm::dw_tile must choose them
 CASES = [
-    _w(1, 72, 4, 2, 40),                       # one token, two empty slots: 32-row tile, one slab with a remainder
-    _w(33, 200, 6, 2, 136, ns=1),              # r = 14
-    _w(130, 264, 8, 4, 136),                   # r = 65: 64-row tile
-    _w(150, 136, 4, 2, 24, ns=1),              # r = 90 but few tiles: 64-row tile
-    _w(800, 1032, 64, 8, 264),                 # r = 100: 64-row tile, 128-row dW tile
-    _w(1600, 520, 64, 8, 776, bias="zipf"),    # r = 200: 128-row tile, 128-row dW tiles
-    _w(2400, 520, 64, 8, 776),                 # r = 300: large tiles throughout
-    _w(700, 136, 4, 2, 72),                    # r = 350: large tile, 64-row dW tile
-    _w(2, 40, 4, 1, 24, "f32"),                # fp32, empty slots, k below one slab
-    _w(40, 136, 8, 4, 72, "f32", ns=1),        # r = 22: 32-row tile
-    _w(300, 1032, 5, 3, 264, "f32", bias="zipf"),   # r = 180, few tiles: 32-row tile, 64-row and split-k dW tiles
-    _w(1200, 264, 16, 4, 520, "f32"),          # r = 300: 64-row tile
+    (_w(1, 72, 4, 2, 40), "32 64 64"),                     # one token, two empty slots, one slab with a remainder
+    (_w(33, 200, 6, 2, 136, ns=1), "32 64 64"),            # r = 14
+    (_w(130, 264, 8, 4, 136), "64 64 64"),                 # r = 65
+    (_w(150, 136, 4, 2, 24, ns=1), "64 64 64"),            # r = 90
+    (_w(800, 1032, 64, 8, 264), "64 128 128"),             # r = 100
+    (_w(1600, 520, 64, 8, 776, bias="zipf"), "128 128 128"),   # r = 200
+    (_w(2400, 520, 64, 8, 776), "large large large"),      # r = 300
+    (_w(700, 136, 4, 2, 72), "large 64 64"),               # r = 350
+    (_w(5, 1032, 64, 8, 264), "32 128 128"),               # empty slots on 128 x 128 weight-gradient tiles
+    (_w(2, 40, 4, 1, 24, "f32"), "32 split split"),        # fp32, empty slots, k below one slab
+    (_w(40, 136, 8, 4, 72, "f32", ns=1), "32 split split"),    # r = 22
+    (_w(300, 1032, 5, 3, 264, "f32", bias="zipf"), "32 64 64"),   # r = 180, few row tiles
+    (_w(700, 136, 4, 2, 72, "f32"), "32 split split"),     # r = 350: ring buffers of the k split reused twice
+    (_w(1200, 264, 16, 4, 520, "f32"), "64 64 64"),        # r = 300
+    (_w(3, 264, 16, 4, 520, "f32"), "32 64 64"),           # empty slots on 64 x 64 weight-gradient tiles
 ]
 
 
-@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [w for w, _ in CASES], ids=lambda w: w.name)
 def test_step(w):
     inp = LayerInputs(w)
     ref = OracleLayer(w, inp)
@@ -53,6 +57,8 @@ def test_step(w):
     log(w.name)
     r.forward(idx=torch.from_numpy(ref.idx.astype(np.int32)).cuda(),
               gate=torch.from_numpy(ref.gate.astype(np.float32)).cuda())
+    for t in (r.dWg, r.dWu, r.dWd):
+        t.fill_(float("nan"))                    # a gradient is written, not added to what was there
     r.backward(dgate=True)
     u = torch.empty(r.S_r + w.n_shared, dtype=torch.float32, device="cuda")
     api.moe_expert_utility(r.layer_tables, r.x_sq, r.dy_sq, r.perm_token, r.perm_gate, r.offsets, w.T, w.k, r.ws_bwd, u)
@@ -67,12 +73,16 @@ def test_step(w):
     once = []
     for i, s in enumerate(r.tuning_slots):
         got = [host(t[i]).copy() for t in (r.dWg, r.dWu, r.dWd)]
-        once.append(got)
         for a, b in zip(got, dW[s]):
             if not np.any(b):
-                assert not a.any()               # an empty tuning slot: exact zeros
+                assert not a.any()               # an empty tuning slot: exact zeros (not NaN)
             else:
                 assert rel_fro(a, b) <= tol
+        if not np.any(dW[s][0]):
+            for t in (r.dWg, r.dWu, r.dWd):      # what an earlier micro-batch left in such a slot stays
+                t[i].fill_(3.0)
+            got = [np.full_like(a, 1.5) for a in got]
+        once.append(got)
     r.backward(accumulate_dw=True)               # the same step again: fp32 x + x
     torch.cuda.synchronize()
     for i, got in enumerate(once):

@@ -25,6 +25,14 @@ def plan(d, I, S, ns, T, k, dtype="bf16"):
     return ROWS[p.rows], DW[p.dw]
 
 
+def dw_tiles(d, I, S, ns, dtype="bf16"):
+    """The small tiles of dW_down and dW_gate/up."""
+    f = getattr(api.lib(), "_ZN2fm7dw_tileEPK9moe_layerb")       # fm::dw_tile(const moe_layer*, bool)
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_bool]
+    L = api.moe_layer(d, I, api.MOE_BF16 if dtype == "bf16" else api.MOE_F32, S, ns, *[None] * 6)
+    return tuple(("split", "64", "128")[f(ctypes.addressof(L), gate_up)] for gate_up in (False, True))
+
+
 def q8_rows(d, I, S, ns, T, k):
     """Rows of the int8 forward's row tile."""
     f = getattr(api.lib(), "_ZN2fm7q8_tileEPK12moe_layer_q8ii")   # fm::q8_tile(const moe_layer_q8*, int, int)
@@ -88,6 +96,13 @@ def test_rows_that_must_not_depend_on_the_tile_cover_every_tile():
     for c, rows in G.Q8_SAME:
         for n, tile in rows.items():
             assert q8_rows(c["d"], c["I"], c["S"], 0, c["S"] * n, 1) == tile
+
+
+@pytest.mark.parametrize("w,want", G.CASES, ids=lambda x: getattr(x, "name", None))
+def test_step_cases_take_their_tiles(w, want):
+    rows, dw = plan(w.d, w.I, w.E, w.n_shared, w.T, w.k, w.dtype)
+    got = (rows,) + (("large",) * 2 if dw == "large" else dw_tiles(w.d, w.I, w.E, w.n_shared, w.dtype))
+    assert " ".join(got) == want
 
 
 @pytest.mark.parametrize("name", list(G.Q8_TILES))
