@@ -577,8 +577,10 @@ __global__ __launch_bounds__(256, C::BPC) void kt_q8_down(Q8Ptrs W, const bf16* 
 
 // ------------------------------------------------------------------ host ----
 
-// (Tile indices fit in 32 bits: a tile writes at least 16 KB of output, so 2^31
-// of them would not fit in memory.)
+// (Tile indices fit in 32 bits.  A row product has at most rows / RA + slots row tiles:
+// the full ones write 4 KB or more per column tile, so 2^31 would not fit in memory,
+// and the partial ones, one per slot, come to no more than the 32-column blocks of the
+// slots' weights.  A weight-gradient tile writes at least 8 x 8 values of 4 bytes.)
 // Blocks for at most `tiles` tiles, BPC per compute unit, a multiple of the XCDs.
 template <class C> dim3 tile_grid(long long tiles) {
   const long long most = (long long)persistent_blocks() * C::BPC;

@@ -60,19 +60,8 @@ struct AccCoord {
   int row, col4;
 };
 
-// 4 consecutive values <-> global memory of T.
-__device__ __forceinline__ void store4(bf16* p, f32x4_t v) {
-  u32x2_t o;
-  o[0] = pk_bf16(v[0], v[1]);
-  o[1] = pk_bf16(v[2], v[3]);
-  *(FM_GLOBAL u32x2_t*)(p) = o;
-}
+// 4 consecutive values <-> global memory.
 __device__ __forceinline__ void store4(float* p, f32x4_t v) { *(FM_GLOBAL f32x4_t*)(p) = v; }
-__device__ __forceinline__ f32x4_t load4(const bf16* p) {
-  const u32x2_t w = *(const FM_GLOBAL u32x2_t*)(p);
-  return f32x4_t{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xFFFF0000u),
-                 __uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xFFFF0000u)};
-}
 __device__ __forceinline__ f32x4_t load4(const float* p) { return *(const FM_GLOBAL f32x4_t*)(p); }
 
 // Tile configuration: RA x RB block tile, WM x WN waves, BK k per slab,

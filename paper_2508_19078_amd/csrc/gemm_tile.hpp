@@ -291,8 +291,8 @@ template <int N, int INS> __device__ __forceinline__ void tile_wait(int after) {
   }
 }
 
-// acc += A B^T over [0, K) (and over [0, K) of the second pair with TWO).  The
-// LDS must be free on entry and is free on return (a barrier ends the call).
+// acc += A B^T over [0, K), K >= 1 (and over [0, K) of the second pair with TWO).
+// The LDS must be free on entry and is free on return (a barrier ends the call).
 // Slab kt has landed once at most the NS - 2 slabs issued after it are in
 // flight; the barrier at the top of slab kt says that every wave has read slab
 // kt - 1, whose buffer then takes slab kt + NS - 1.  A wave issues a slab's
@@ -308,10 +308,6 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
   typedef typename tile_frag<T>::type frag;
   const int n1 = (K + C::BK - 1) / C::BK;
   const int nk = TWO ? 2 * n1 : n1;
-  if (nk == 0) {   // no rows: the accumulators stay zero
-    tile_barrier();
-    return;
-  }
   const int wave = tile_wave<C>();
   TileDma<T, AKC, C::RA, AI, C::KR> da;
   std::conditional_t<I8, TileDmaI8<C::RB, BI>, TileDma<T, BKC, C::RB, BI, C::KR>> db;
