@@ -323,7 +323,7 @@ __device__ __forceinline__ void tile_gemm(const TileSrc<typename C::T>& A, const
   // (fp32, 75 rows per slot, d = 3480, I = 712: forward 1990 -> 1860 us, backward
   // 2655 -> 2555; a branch inside the slab loop instead cost full tiles 5-15 %)
   auto phys = [](int r, bool inter) { return inter ? 32 * (r >> 6) + (r & 31) : r; };
-  const bool works = wave < C::MW && phys(row0, AI) < A.rows && phys(col0, BI) < B.rows;
+  const bool works = (C::MW == 4 || wave < C::MW) && phys(row0, AI) < A.rows && phys(col0, BI) < B.rows;
   constexpr int KW = C::KS / C::WK;   // steps per wave and slab
   // steps whose fragments are read ahead (all, where the registers allow)
   constexpr int SB = C::MI * C::NJ >= 8 && KW > 2 ? 2 : KW;
