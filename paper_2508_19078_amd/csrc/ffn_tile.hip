@@ -639,9 +639,15 @@ template <class Fn> void with_rows(const TilePlan& p, int dtype, Fn fn) {
 // 40, 34; I = 256, d = 512, 16 slots, r = 2048 (128, 256 tiles) 66, 112 and 79,
 // 123; I = 376, d = 712, 32 slots, r = 375 (576, 1152) 35, 40 and 52, 55; I =
 // 1408, d = 2048, 64 slots, r = 96 114, 99 and 250, 187.
-DwTile dw_tile_of(int dtype, long long tiles128) {
+// Above 512 rows per slot that holds only where a slot has few tiles, so that the
+// rows of a popular slot make a tail (48 of 128 x 128; us of the whole backward): I =
+// 2376, d = 984, 3 slots (152, 304 tiles per slot) r = 1000 211, 186; r = 16000 3130,
+// 2130; I = 256, d = 4096, 8 slots (64, 128) r = 2000 419, 365; I = 512, d = 1024, 16
+// slots (32, 64) r = 1000 232, 229; r = 8000 1657, 1342; I = d = 256, 64 slots (4, 8) r
+// = 2000 474, 520, Zipf 692, 857.
+DwTile dw_tile_of(int dtype, long long tiles128, int S, double r) {
   if (dtype == MOE_F32) return 4 * tiles128 < 512 ? DW_SPLIT_K : DW_64;
-  return tiles128 < 1280 ? DW_64 : DW_128;
+  return tiles128 >= 1280 || (r > 512 && tiles128 >= 48LL * S) ? DW_128 : DW_64;
 }
 template <class Fn> void with_dw(DwTile t, int dtype, Fn fn) {
   if (dtype == MOE_F32) {
@@ -718,7 +724,7 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   else p.rows = TilePlan::ROWS_128;
   // Weight gradients, us of the backward on the tiles of with_dw and on the large
   // ones.  The large ones need four tiles per compute unit (every slot counted as
-  // tuning), and slots of about 256 rows: I = 1408, d = 2048, 64 slots r = 176 1065,
+  // tuning), and slots of about 288 rows: I = 1408, d = 2048, 64 slots r = 176 1065,
   // 1095; r = 272 1266, 1272; r = 340 1408, 1352; I = 688, d = 4096, 16 slots r = 176
   // 376, 380; r = 304 427, 424.  About 100 rows are enough where I is a multiple of 256
   // and d >= 3072 (the small tiles read half lines, here of rows a multiple of 512
@@ -726,17 +732,33 @@ TilePlan tile_plan(const moe_layer* L, int T, int k) {
   // 4096, 64 slots r = 240 592, 542; I = 1536, d = 3072, 24 slots r = 112 648, 657, r =
   // 240 779, 751; and in the widest layers (d = 4096, I = 1408, 128 slots: r = 112
   // 3362, 3372; r = 240 4592, 4276).
-  // Too few tiles (large, small, for dW_down + dW_gate/up): I = 512, d = 768, 32 slots
-  // (384) r = 512 173, 127; I = 256, d = 512, 16 slots r = 2048 323, 145.
+  // Two tiles per compute unit are enough once a tile is long and a slot has 32 of them
+  // (with fewer a popular slot's tiles make a tail: I = 280, d = 712, 98 slots, 882
+  // tiles, r = 2315, Zipf 1734, 1981): I = 1408, d = 2048, 8 slots (704 tiles) r = 1000
+  // 413, 408; r = 4000 1387, 1170; I = 688, d = 2048, 12 slots (576) r = 1000 377, 376; r
+  // = 4000 1180, 1065; I = 768, d = 1536, 16 slots (576) r = 2000 648, 688; r = 8000
+  // 2373, 2207; I = d = 1024, 16 slots (512) r = 1500 496, 486; r = 4000 1137, 1102.
+  // Fewer never gained: I = 1408, d = 2048, 4 slots (352) r = 4000 740, 796; I = 512, d =
+  // 768, 32 slots (384) r = 4000 1135, 1280; I = 512, d = 1024, 16 slots (256) r = 4000
+  // 725, 853.  Except where the tokens' choices fill every slot alike (k >= S_routed, no
+  // popular slot): I = 2376, d = 984, 3 slots (228) r = 2000 294, 287; r = 20000 2377,
+  // 2026; I = 1408, d = 2048, 2 slots (176) r = 2000 195, 202; r = 8000 676, 598; I =
+  // 2048, d = 768, 3 slots (144) r = 4000 374, 354; not I = d = 1024, 3 slots (96) r =
+  // 20000 1087, 1231.
   const double dw256 = (double)S * ((L->I + 127) / 128) * ((L->d + 255) / 256);
   const bool dw_early = dw256 >= 8192 || (L->I % 256 == 0 && L->d >= 3072);
-  p.dw = dw256 >= 1024 && r > (dw_early ? 100 : 256) ? TilePlan::LARGE_DW : TilePlan::SMALL_DW;
+  const bool full = k >= L->S_routed;
+  const bool dw_large = dw256 >= 1024 ? r > (dw_early ? 100 : 288)
+                              : full ? dw256 >= 128 && r * dw256 >= 5e5
+                                     : dw256 >= 512 && dw256 >= 32 * S && r * dw256 >= 1e6;
+  p.dw = dw_large ? TilePlan::LARGE_DW : TilePlan::SMALL_DW;
   return p;
 }
 
-DwTile dw_tile(const moe_layer* L, bool gate_up) {
-  const long long S = L->S_routed + L->S_shared;
-  return dw_tile_of(L->dtype, S * cdiv(L->d, 128) * cdiv(L->I, gate_up ? 64 : 128));
+DwTile dw_tile(const moe_layer* L, int T, int k, bool gate_up) {
+  const int S = L->S_routed + L->S_shared;
+  return dw_tile_of(L->dtype, (long long)S * cdiv(L->d, 128) * cdiv(L->I, gate_up ? 64 : 128), S,
+                    (double)T * (k + L->S_shared) / S);
 }
 
 int tile_norm_cols(const moe_layer* L, const TilePlan& p) {
@@ -784,13 +806,13 @@ void tile_dx(const TilePlan& p, const moe_layer* L, const int32_t* offsets, int 
 void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* offsets, int Tn, int k, const void* H,
              const void* dO, const void* dAg, const void* dAu, int ldA, int accumulate, hipStream_t st) {
   const RowArgs ra = row_args(L, offsets, Tn, k, ldA);
-  with_dw(dw_tile(L, false), L->dtype, [&](auto c) {
+  with_dw(dw_tile(L, Tn, k, false), L->dtype, [&](auto c) {
     typedef decltype(c) C;
     typedef typename C::T T;
     hipLaunchKernelGGL(kt_dw_d<C>, tile_grid<C>((long long)ra.S * cdiv(ra.d, C::RA) * cdiv(ra.I, C::RB)), dim3(256), 0,
                        st, layer_ptrs<T>(L), (const T*)dO, (const T*)H, ra, accumulate);
   });
-  with_dw(dw_tile(L, true), L->dtype, [&](auto c) {
+  with_dw(dw_tile(L, Tn, k, true), L->dtype, [&](auto c) {
     typedef decltype(c) C;
     typedef typename C::T T;
     hipLaunchKernelGGL(kt_dw_gu<C>, tile_grid<C>((long long)ra.S * cdiv(ra.I, C::RA / 2) * cdiv(ra.d, C::RB)),

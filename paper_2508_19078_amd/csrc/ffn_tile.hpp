@@ -16,7 +16,7 @@ TilePlan tile_plan(const moe_layer* L, int T, int k);
 // The tile of a small-tile weight gradient: 64 x 32 with k split (fp32), 64 x 64 (fp32)
 // or 64 x 128 (bf16), 128 x 128 (bf16).
 enum DwTile { DW_SPLIT_K, DW_64, DW_128 };
-DwTile dw_tile(const moe_layer* L, bool gate_up);
+DwTile dw_tile(const moe_layer* L, int T, int k, bool gate_up);
 // Columns of I per partial of the utility's row norms (the dH column tile).
 int tile_norm_cols(const moe_layer* L, const TilePlan& p);
 constexpr int NORM_COLS_MIN = 64;   // the fewest that any plan takes

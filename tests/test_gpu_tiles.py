@@ -37,6 +37,7 @@ CASES = [
     (_w(1600, 520, 64, 8, 776, bias="zipf"), "128 128 128"),   # r = 200
     (_w(2400, 520, 64, 8, 776), "large large large"),      # r = 300
     (_w(700, 136, 4, 2, 72), "large 64 64"),               # r = 350
+    (_w(1100, 776, 2, 1, 1032), "large 128 128"),          # r = 550, few slots of many tiles
     (_w(5, 1032, 64, 8, 264), "32 128 128"),               # empty slots on 128 x 128 weight-gradient tiles
     (_w(2, 40, 4, 1, 24, "f32"), "32 split split"),        # fp32, empty slots, k below one slab
     (_w(40, 136, 8, 4, 72, "f32", ns=1), "32 split split"),    # r = 22

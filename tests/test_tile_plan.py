@@ -25,12 +25,12 @@ def plan(d, I, S, ns, T, k, dtype="bf16"):
     return ROWS[p.rows], DW[p.dw]
 
 
-def dw_tiles(d, I, S, ns, dtype="bf16"):
+def dw_tiles(d, I, S, ns, T, k, dtype="bf16"):
     """The small tiles of dW_down and dW_gate/up."""
-    f = getattr(api.lib(), "_ZN2fm7dw_tileEPK9moe_layerb")       # fm::dw_tile(const moe_layer*, bool)
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_bool]
+    f = getattr(api.lib(), "_ZN2fm7dw_tileEPK9moe_layeriib")     # fm::dw_tile(const moe_layer*, int, int, bool)
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_bool]
     L = api.moe_layer(d, I, api.MOE_BF16 if dtype == "bf16" else api.MOE_F32, S, ns, *[None] * 6)
-    return tuple(("split", "64", "128")[f(ctypes.addressof(L), gate_up)] for gate_up in (False, True))
+    return tuple(("split", "64", "128")[f(ctypes.addressof(L), T, k, gate_up)] for gate_up in (False, True))
 
 
 def q8_rows(d, I, S, ns, T, k):
@@ -61,13 +61,53 @@ TIMED = [
     ((768, 512, 64, 100), ("64", "small")),
     ((768, 512, 64, 240), ("128", "small")),
     ((512, 256, 16, 2000), ("large", "small")),       # weight gradients 145 us small, 323 large
+    ((2048, 1408, 8, 4000), ("large", "large")),      # backward 1170 us large, 1387 small
+    ((2048, 688, 12, 4000), ("large", "large")),      # 1065, 1180
+    ((2048, 1408, 4, 4000), ("large", "small")),      # 796, 740
+    ((768, 512, 32, 4000), ("large", "small")),       # 1280, 1135
+    ((712, 280, 98, 2315), ("large", "small")),       # Zipf 1981, 1734
 ]
 
 
 @pytest.mark.parametrize("shape,want", TIMED)
 def test_timed_shapes(shape, want):
     d, I, S, r = shape
-    assert plan(d, I, S, 0, r * S // 4, 4) == want
+    k = 4 if S > 4 else 1
+    assert plan(d, I, S, 0, r * S // k, k) == want
+
+
+# The same of layers whose every slot holds every token: weight gradients
+FULL_TIMED = [
+    ((984, 2376, 3, 20000), "large"),      # backward 2026 us large, 2377 small
+    ((2048, 1408, 2, 1500), "small"),      # r = 2000: 202, 195
+    ((2048, 1408, 2, 8000), "large"),      # 598, 676
+    ((768, 2048, 3, 4000), "large"),       # 354, 374
+    ((1024, 1024, 3, 20000), "small"),     # 1231, 1087
+]
+
+
+@pytest.mark.parametrize("shape,want", FULL_TIMED)
+def test_timed_full_slots(shape, want):
+    d, I, S, T = shape
+    assert plan(d, I, S, 0, T, S)[1] == want
+    assert plan(d, I, 0, S, T, 1)[1] == want            # shared experts only
+
+
+# Rows per slot and the small tiles of dW_down and dW_gate/up
+DW_TIMED = [
+    ((984, 2376, 3, 400), ("64", "64")),
+    ((984, 2376, 3, 16000), ("128", "128")),          # backward 2130 us, 3130 on 64 x 128 tiles
+    ((4096, 256, 8, 2000), ("128", "128")),           # 365, 419
+    ((1024, 512, 16, 8000), ("64", "128")),
+    ((256, 256, 64, 2000), ("64", "64")),             # 520, 474 (Zipf 857, 692)
+    ((2048, 1408, 64, 96), ("128", "128")),
+]
+
+
+@pytest.mark.parametrize("shape,want", DW_TIMED)
+def test_timed_weight_gradient_shapes(shape, want):
+    d, I, S, r = shape
+    assert dw_tiles(d, I, S, 0, r * S, 1) == want
 
 
 # The int8 forward, gate-up + down in us on 128 and 256 rows
@@ -101,7 +141,7 @@ def test_rows_that_must_not_depend_on_the_tile_cover_every_tile():
 @pytest.mark.parametrize("w,want", G.CASES, ids=lambda x: getattr(x, "name", None))
 def test_step_cases_take_their_tiles(w, want):
     rows, dw = plan(w.d, w.I, w.E, w.n_shared, w.T, w.k, w.dtype)
-    got = (rows,) + (("large",) * 2 if dw == "large" else dw_tiles(w.d, w.I, w.E, w.n_shared, w.dtype))
+    got = (rows,) + (("large",) * 2 if dw == "large" else dw_tiles(w.d, w.I, w.E, w.n_shared, w.T, w.k, w.dtype))
     assert " ".join(got) == want
 
 
