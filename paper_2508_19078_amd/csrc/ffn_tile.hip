@@ -834,16 +834,19 @@ void tile_dw(const moe_layer* L, const void* X, const void* Xp, const int32_t* o
 // us on 128, 256 rows: 64 slots, d = 2048, I = 1408 r = 512 615, 645; r = 1024 1174,
 // 1146; r = 4096 4665, 4278; d = 4096, I = 1024 r = 4096 6945, 6203; d = 1024, I = 2816 r
 // = 768 944, 971; r = 2048 2395, 2363; 8 slots, d = 4096, I = 2816 r = 512 290, 305; r =
-// 2048 1034, 996; r = 8192 4286, 3822.  Layers of few or short products never gained:
-// 16 slots, d = 4096, I = 688 r = 2048 638, 690; r = 8192 2457, 2448; 32 slots, d = 1024,
-// I = 512 r = 8192 936, 981.
+// 2048 1034, 996; r = 8192 4286, 3822; 4 slots r = 2000 569, 552; r = 10000 2621, 2436.
+// Smaller layers need more rows: 16 slots, d = 4096, I = 688 r = 2048 638, 690; r = 4096
+// 1228, 1272; r = 8192 2457, 2448; 8 slots, d = 2048, I = 1408 r = 2000 300, 310; r =
+// 10000 1395, 1324; 16 slots, d = I = 1024 r = 5000 566, 596; r = 10000 1114, 1072; 32
+// slots, d = 1024, I = 512 r = 8192 936, 981; the smallest never gained: 3 slots, d =
+// 976, I = 2368 r = 5000 242, 276; r = 20000 952, 954.
 int q8_tile(const moe_layer_q8* L, int T, int k) {
   const int S = L->S_routed + L->S_shared;
   const double r = (double)T * (k + L->S_shared) / S;
   const double active = (double)((long long)T * k < L->S_routed ? (long long)T * k : L->S_routed) + L->S_shared;
   if (r <= 64 && active * ((2LL * L->I + 127) / 128) < 768) return 32;
   const double layer = (double)S * L->d * L->I;
-  if (layer >= 5e7 && r * r * layer >= 1.5e14) return 256;
+  if (r * r * layer >= (layer >= 4.6e7 ? 1.5e14 : 1.2e15) && layer >= 1e7) return 256;
   return r >= 72 && S * (r / 128 + 0.5) * ((L->I + 127) / 128) >= 288 ? 128 : 64;
 }
 

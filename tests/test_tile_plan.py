@@ -120,6 +120,10 @@ Q8_TIMED = [
     ((4096, 2816, 8, 2048), 256),     # 1034, 996
     ((4096, 688, 16, 2048), 128),     # 638, 690
     ((1024, 512, 32, 8192), 128),     # 936, 981
+    ((4096, 2816, 4, 2000), 256),     # 569, 552
+    ((1024, 1024, 16, 5000), 128),    # 566, 596
+    ((1024, 1024, 16, 10000), 256),   # 1114, 1072
+    ((976, 2368, 3, 20000), 128),     # 952, 954
 ]
 
 
